@@ -109,7 +109,8 @@ typedef struct {
  * (tx*ty == 256, tx in {16, 32, 64}), each carving tz samples stacked in z. */
 typedef struct {
     int32_t tx, ty, tz;
-    int32_t persistent_blocks; /* workgroups of the persistent batched launch; 0 = auto */
+    int32_t persistent_blocks; /* workgroups of a frame's fine carve and of a batched carve
+                                  whose depth is not 4; 0 = auto */
 } fvv_tile;
 
 typedef struct fvv_ctx fvv_ctx;
@@ -220,9 +221,10 @@ fvv_status fvv_surface_noalloc(const fvv_grid *roi, const uint8_t *d_occ_fine, i
  * With tile->tz == 4 (and for tile == NULL, the default 64x4x4 tile) the
  * cameras are culled per 4x4x4 box of samples (a camera whose padded pixel
  * rectangle over the box holds no foreground rejects the box; one whose
- * rectangle is all foreground accepts it) and the tiles are split statically
- * over the XCDs; other depths test every sample against every camera, the
- * workgroups taking tiles from a device counter.  A job with n_cams outside
+ * rectangle is all foreground accepts it) and the work is split statically
+ * over the XCDs, whatever the tile's width and workgroups; other depths test every sample
+ * against every camera, the workgroups taking tiles from a device counter.
+ * Until the call's work is done the output may hold other bytes than 0 and 1.  A job with n_cams outside
  * 1..FVV_MAX_CAMS, an image side outside 1..65536, an empty lattice or a
  * negative base or offset is skipped, and the next fvv_check reports
  * FVV_EINVAL.  Calls on one context must not overlap (they share its

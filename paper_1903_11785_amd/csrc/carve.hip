@@ -454,9 +454,57 @@ __device__ __forceinline__ bool job_ok(const fvv_job& j) {
            j.out_offset >= 0;
 }
 
-// Prefix sums of tile and tile-row counts over a host-given job table; resets
-// the work counter.  counter[0] = next work item, [1] = tiles per item,
-// [2] = jobs.  A job out of range gets no tiles and raises the job flag.
+// The units of a culled batched carve: kUnitY sample rows of 4 layers, all
+// along x, y fastest, the rows padded to groups of kUnitGroup units.
+constexpr int kUnitY = 16, kUnitGroup = 4;
+
+__device__ __forceinline__ uint64_t units_of_grid(const fvv_grid& g) {
+    constexpr int kRows = kUnitY * kUnitGroup;
+    return kUnitGroup * (uint64_t)((g.dims[1] + kRows - 1) / kRows) * (uint64_t)((g.dims[2] + 3) / 4);
+}
+
+// Prefix sums over a host-given job table by one workgroup: of tiles (TX x
+// TZ), or with kUnits of units; resets the work counter.  counter[0] = next
+// work item, [1] = tiles per item, [2] = jobs.  A job out of range gets no
+// tiles and raises the job flag.
+template <int TX, int TZ, bool kUnits>
+__device__ __forceinline__ void batched_prefix(const fvv_job* __restrict__ jobs, uint32_t n_jobs,
+                                               JobPrefix* __restrict__ pre,
+                                               uint32_t* __restrict__ counter,
+                                               uint32_t* __restrict__ status, uint32_t blocks) {
+    __shared__ uint64_t scratch[kBlock / kWave];
+    __shared__ uint64_t carry;
+    if (threadIdx.x == 0)
+        carry = 0;
+    __syncthreads();
+    for (uint32_t base = 0; base < n_jobs; base += kBlock) {
+        uint32_t j = base + threadIdx.x;
+        uint64_t t = 0;
+        if (j < n_jobs) {
+            if (job_ok(jobs[j]))
+                t = kUnits ? units_of_grid(jobs[j].grid) : tiles_of_grid(jobs[j].grid, TX, TZ);
+            else
+                atomicOr(status, kFlagJob);
+        }
+        uint64_t tot;
+        const uint64_t ex = block_exclusive_sum64<kBlock>(t, scratch, &tot);
+        const uint64_t c0 = carry;
+        if (j < n_jobs)
+            pre[j].tile_off = c0 + ex;
+        __syncthreads();
+        if (threadIdx.x == 0)
+            carry = c0 + tot;
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        uint64_t total = carry;
+        pre[n_jobs].tile_off = total;
+        counter[0] = 0;
+        counter[1] = grab_size(total, blocks);
+        counter[2] = n_jobs;
+    }
+}
+
 template <int TX, int TZ>
 __global__ __launch_bounds__(kBlock) void batched_prepare_kernel(const fvv_job* __restrict__ jobs,
                                                                  uint32_t n_jobs,
@@ -464,65 +512,7 @@ __global__ __launch_bounds__(kBlock) void batched_prepare_kernel(const fvv_job* 
                                                                  uint32_t* __restrict__ counter,
                                                                  uint32_t* __restrict__ status,
                                                                  uint32_t blocks) {
-    __shared__ uint64_t scratch[kBlock / kWave];
-    __shared__ uint64_t carry, carry_rows;
-    if (threadIdx.x == 0) {
-        carry = 0;
-        carry_rows = 0;
-    }
-    __syncthreads();
-    for (uint32_t base = 0; base < n_jobs; base += kBlock) {
-        uint32_t j = base + threadIdx.x;
-        uint64_t t = 0, rows = 0;
-        if (j < n_jobs) {
-            if (job_ok(jobs[j])) {
-                t = tiles_of_grid(jobs[j].grid, TX, TZ);
-                rows = t / (uint64_t)((jobs[j].grid.dims[0] + TX - 1) / TX);
-            } else {
-                atomicOr(status, kFlagJob);
-            }
-        }
-        uint64_t tot, tot_rows;
-        const uint64_t ex = block_exclusive_sum64<kBlock>(t, scratch, &tot);
-        const uint64_t ex_rows = block_exclusive_sum64<kBlock>(rows, scratch, &tot_rows);
-        const uint64_t c0 = carry, r0 = carry_rows;
-        if (j < n_jobs) {
-            pre[j].tile_off = c0 + ex;
-            pre[j].row_off = r0 + ex_rows;
-        }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            carry = c0 + tot;
-            carry_rows = r0 + tot_rows;
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        uint64_t total = carry;
-        pre[n_jobs].tile_off = total;
-        pre[n_jobs].row_off = carry_rows;
-        counter[0] = 0;
-        counter[1] = grab_size(total, blocks);
-        counter[2] = n_jobs;
-    }
-}
-
-// Rounding pad of every (job, camera) pair over the job's lattice box, for the
-// camera culling of the batched carve: job_pad[j * FVV_MAX_CAMS + c].
-__global__ __launch_bounds__(kBlock) void job_pad_kernel(const fvv_job* __restrict__ jobs,
-                                                         uint32_t n_jobs,
-                                                         const fvv_camera* __restrict__ cams,
-                                                         float* __restrict__ job_pad) {
-    const uint64_t p = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (p >= (uint64_t)n_jobs * FVV_MAX_CAMS)
-        return;
-    const fvv_job& j = jobs[p / FVV_MAX_CAMS];
-    const int c = (int)(p % FVV_MAX_CAMS);
-    if (!job_ok(j) || c >= j.n_cams)
-        return;
-    double lo[3], hi[3];
-    grid_box(j.grid, lo, hi);
-    job_pad[p] = rounding_pad(cams[j.cam_base + c].P, j.width, j.height, lo, hi);
+    batched_prefix<TX, TZ, false>(jobs, n_jobs, pre, counter, status, blocks);
 }
 
 template <int TX, int TZ, bool kFineBits>
@@ -716,8 +706,9 @@ __device__ __forceinline__ int classify_box(const Cams& cams, int c,
 // l%8) and reduce the corner bounds over 8 lanes, then test row l%16 of the
 // rectangle (rectangles of more than 16 rows or kWords words count as mixed).
 // Returns, uniform over the wave, the cameras that reject every sample of the
-// box and those that are mixed; the others accept every sample.
-template <int kWords, class Cams>
+// box and those that are mixed; the others accept every sample.  kStop: leave
+// after the first pass with a rejecting camera (mixed is then incomplete).
+template <int kWords, bool kStop = false, class Cams>
 __device__ __forceinline__ void classify_box_wave(const Cams& cams,
                                                   const uint32_t* __restrict__ sils,
                                                   int64_t cam_words, const float* lo,
@@ -755,6 +746,8 @@ __device__ __forceinline__ void classify_box_wave(const Cams& cams,
             reject |= (uint32_t)((rb >> (16 * g)) & 1u) << (cb + g);
             mixed |= (uint32_t)((mb >> (16 * g)) & 1u) << (cb + g);
         }
+        if (kStop && reject != 0u)
+            return;
     }
 }
 
@@ -1702,117 +1695,464 @@ __global__ __launch_bounds__(kBlock, 7) void carve_frame_kernel(const fvv_job* _
 #endif
 }
 
-// The batched carve with camera culling: the tile rows (the tiles of one job
-// that share y and z, i.e. all its tiles along x) of all jobs in a static
-// XCD-aware partition; each job's cameras from the device table and its
-// rounding pads from job_pad_kernel.  A workgroup carves whole tile rows, so
-// it writes every byte of the TY rows x 4 layers of output samples the row
-// covers: each layer's TY sample rows are contiguous in the output, and cache
-// lines are written whole by one workgroup (partly written lines are what
-// costs HBM write traffic here).  Along the row, each wave classifies one
-// tile of a group of four for its whole box (four latency chains of job,
-// camera and silhouette loads in flight at once), then the workgroup carves
-// the group's tiles one after the other, writing rejected tiles as zeros
-// directly.  The tile-row prefix is read from LDS when the job table fits.
+// ------------------------------------------------------------------ batched carve, culled
+// Most of a batch is empty (98.6 % on 64 frames x 12 ROIs of two ellipsoids),
+// so what it cannot do without is writing zeros.  Three passes:
+//   1. batched_zero_kernel zeroes every job's output, each workgroup a
+//      contiguous part of a job, as fast as a plain fill; its first workgroups
+//      write the unit prefix and the rounding pads.
+//   2. batched_mark_kernel classifies the cameras for units (kUnitY sample
+//      rows x 4 layers, all along x), a wave per kUnitGroup of them, the group
+//      as a whole first, and then for the tiles (16 samples along x) of a unit
+//      that no camera rejects, 16 at a time.  Such a unit's tiles get a mark
+//      in their first byte: kLiveMark, or kDeadMark where a camera rejects the
+//      tile.
+//   3. carve_batched_culled_kernel carves the live tiles of the marked units,
+//      a wave each.
+// The units and tiles go to the XCDs in a static partition; each job's cameras
+// come from the device table.  64 frames x 12 ROIs (2.9e9 samples, 4 cameras)
+// take 522 + 104 + 200 us; one pass that classified and wrote a row of tiles
+// per workgroup and step took 1258 us, 2.3 TB/s.  A first pass that zeroed the
+// rejected units itself took 636 us whatever it classified: its 2.5 KB spans
+// at odd addresses reach 4.2 TB/s.
 constexpr int kBatchedJobLds = 1024;
 constexpr int kGroup = kBlock / kWave;
-constexpr int kRowRectWords = 8;   // silhouette words per row of a tile row's rectangle
+constexpr int kRowRectWords = 8;   // silhouette words per row of a unit's rectangle
+constexpr uint8_t kLiveMark = 0xff, kDeadMark = 0xfe;   // no occupancy values
 
-// Zero n bytes from p by the workgroup: 16-byte stores between the first and
-// the last 16-byte boundary, byte stores at the ends.
-__device__ __forceinline__ void zero_span(uint8_t* p, int64_t n) {
-    const int64_t head = (int64_t)((16 - ((uintptr_t)p & 15)) & 15);
-    const int64_t h = head < n ? head : n;
-    if ((int64_t)threadIdx.x < h)
-        p[threadIdx.x] = 0;
-    const int64_t n16 = (n - h) / 16;
-    uint4* q = reinterpret_cast<uint4*>(p + h);
-    for (int64_t i = threadIdx.x; i < n16; i += kBlock)
-        q[i] = make_uint4(0u, 0u, 0u, 0u);
-    const int64_t tail0 = h + 16 * n16;
-    if ((int64_t)threadIdx.x < n - tail0)
-        p[tail0 + threadIdx.x] = 0;
+// The first n_off(m) prefixes of the jobs in LDS (kLds) or from the table.
+template <bool kLds>
+struct JobOffsets {
+    const uint64_t* lds;
+    const JobPrefix* pre;
+    __device__ uint64_t operator()(int m) const { return kLds ? lds[m] : pre[m].tile_off; }
+};
+
+template <bool kLds>
+__device__ __forceinline__ JobOffsets<kLds> load_offsets(const JobPrefix* __restrict__ pre,
+                                                         int nj, uint64_t* lds) {
+    if (kLds) {
+        for (int j = threadIdx.x; j <= nj; j += kBlock)
+            lds[j] = pre[j].tile_off;
+        __syncthreads();
+    }
+    return JobOffsets<kLds>{lds, pre};
 }
 
-template <int TX, bool kLds>
+// Unit u of a job: its first row (past the lattice for a padding unit) and
+// layer, and the place of its first byte.
+struct BatchedUnit {
+    int j0, k0;
+    int64_t at;
+};
+
+__device__ __forceinline__ BatchedUnit batched_unit(const fvv_job& job, uint32_t u) {
+    constexpr int kRows = kUnitY * kUnitGroup;
+    const uint32_t nuy = kUnitGroup * (uint32_t)((job.grid.dims[1] + kRows - 1) / kRows);
+    BatchedUnit b;
+    b.j0 = (int)(u % nuy) * kUnitY;
+    b.k0 = (int)(u / nuy) * 4;
+    b.at = job.out_offset +
+           ((int64_t)b.k0 * job.grid.dims[1] + b.j0) * (int64_t)job.grid.dims[0];
+    return b;
+}
+
+__device__ __forceinline__ JobCams job_cams(const fvv_job& job, int j,
+                                            const fvv_camera* __restrict__ cams,
+                                            const float* __restrict__ job_pad) {
+    return JobCams{cams + job.cam_base, job_pad + (int64_t)j * FVV_MAX_CAMS, job.n_cams,
+                   job.width, job.height, (job.width + 31) / 32};
+}
+
+// A job's cameras staged in LDS: P, then the rounding pad.
+struct LdsCams {
+    const float (*cam)[13];
+    int32_t n, W, H, wpr;
+    __device__ const float* Pc(int c) const { return cam[c]; }
+    __device__ float padc(int c) const { return cam[c][12]; }
+};
+
+// Workgroup 0: the unit prefix.  The next pad_blocks: the rounding pad of every
+// (job, camera) pair over the job's lattice box, job_pad[j * FVV_MAX_CAMS + c].
+// The rest, `parts` per job: zeros, each part from one multiple of 4 KB of the
+// address to another (lines are written whole but at a job's ends), 16 bytes a
+// lane.  2.9e9 bytes take 522 us, 5.6 TB/s; in address order over all jobs
+// they take 487, but that needs the prefix first: a launch more, which a small
+// batch (a few us in all) pays as much as a large one.
+__global__ __launch_bounds__(kBlock) void batched_zero_kernel(
+    const fvv_job* __restrict__ jobs, uint32_t n_jobs, const fvv_camera* __restrict__ cams,
+    float* __restrict__ job_pad, JobPrefix* __restrict__ pre, uint32_t* __restrict__ counter,
+    uint32_t* __restrict__ status, uint32_t pad_blocks, uint32_t parts, uint8_t* __restrict__ out) {
+    if (blockIdx.x == 0) {
+        batched_prefix<64, 4, true>(jobs, n_jobs, pre, counter, status, 1u);
+        return;
+    }
+    if (blockIdx.x <= pad_blocks) {
+        const uint64_t p = (uint64_t)(blockIdx.x - 1) * kBlock + threadIdx.x;
+        if (p >= (uint64_t)n_jobs * FVV_MAX_CAMS)
+            return;
+        const fvv_job& j = jobs[p / FVV_MAX_CAMS];
+        const int c = (int)(p % FVV_MAX_CAMS);
+        if (!job_ok(j) || c >= j.n_cams)
+            return;
+        double lo[3], hi[3];
+        grid_box(j.grid, lo, hi);
+        job_pad[p] = rounding_pad(cams[j.cam_base + c].P, j.width, j.height, lo, hi);
+        return;
+    }
+    const uint32_t z = blockIdx.x - 1 - pad_blocks, jn = z / parts, part = z - jn * parts;
+    const fvv_job& j = jobs[jn];
+    if (!job_ok(j))
+        return;
+    constexpr uint64_t kStep = kBlock * 16;
+    const uintptr_t p0 = (uintptr_t)(out + j.out_offset);
+    const uintptr_t p1 = p0 + (uintptr_t)((uint64_t)j.grid.dims[0] * (uint64_t)j.grid.dims[1] *
+                                          (uint64_t)j.grid.dims[2]);
+    const uintptr_t a0 = p0 & ~(uintptr_t)(kStep - 1);
+    const uint64_t steps = (p1 - a0 + kStep - 1) / kStep;
+    for (uint64_t q = steps * part / parts; q < steps * (part + 1) / parts; ++q) {
+        const uintptr_t at = a0 + q * kStep + 16 * threadIdx.x;
+        if (at >= p0 && at + 16 <= p1) {
+            *reinterpret_cast<uint4*>(at) = make_uint4(0u, 0u, 0u, 0u);
+        } else {
+            for (int b = 0; b < 16; ++b)
+                if (at + b >= p0 && at + b < p1)
+                    *reinterpret_cast<uint8_t*>(at + b) = 0;
+        }
+    }
+}
+
+// Pixels [x0, x0 + 31] of a silhouette row of wpr words, bit b = pixel x0 + b
+// (pixels past the row are 0): the two words around x0, kept inside the row.
+__device__ __forceinline__ uint32_t row_window(const uint32_t* __restrict__ row, int wpr, int x0) {
+    const int w = min(x0 >> 5, max(wpr - 2, 0));
+    uint64_t v = row[w];
+    if (wpr > 1)
+        v |= (uint64_t)row[w + 1] << 32;
+    return (uint32_t)(v >> (x0 - 32 * w));
+}
+
+// Classification of camera c for the box of samples with world corners lo, hi
+// by one lane, from the packed rows of its silhouette: rectangles of more than
+// 16 x 32 pixels are mixed; win: the first 8 x 8 pixels of the rectangle, bit
+// 8 r + x, org: its corner (x | y << 16) where it fits those, else kNoWindow.
+template <class Cams>
+__device__ __forceinline__ int classify_small(const Cams& cams, int c,
+                                              const uint32_t* __restrict__ sil, const float* lo,
+                                              const float* hi, uint64_t& win, uint32_t& org) {
+    int cx0, cx1, cy0, cy1;
+    bool inside;
+    const int st = box_rect(cams, c, lo, hi, cx0, cx1, cy0, cy1, inside);
+    win = 0ull;
+    org = kNoWindow;
+    if (st >= 0)
+        return st;
+    if (cy1 - cy0 >= 16 || cx1 - cx0 >= 32)
+        return kCullMixed;
+    const uint32_t m = ~0u >> (31 - (cx1 - cx0));
+    uint32_t any = 0u, all = m;
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {     // rows past the last repeat it
+        const uint32_t v =
+            row_window(sil + (int64_t)min(cy0 + r, cy1) * cams.wpr, cams.wpr, cx0);
+        any |= v & m;
+        all &= v;
+        win |= (uint64_t)(v & 0xffu) << (8 * r);
+    }
+    if (cy1 - cy0 >= 8) {
+#pragma unroll
+        for (int r = 8; r < 16; ++r) {
+            const uint32_t v =
+                row_window(sil + (int64_t)min(cy0 + r, cy1) * cams.wpr, cams.wpr, cx0);
+            any |= v & m;
+            all &= v;
+        }
+    }
+    if (cy1 - cy0 < 8 && cx1 - cx0 < 8)
+        org = (uint32_t)cx0 | ((uint32_t)cy0 << 16);
+    if (any == 0u)
+        return kCullReject;
+    return inside && all == m ? kCullAccept : kCullMixed;
+}
+
+// The four cameras' bits of a ballot over lanes (b, c) = (l % 16, l / 16), ORed.
+__device__ __forceinline__ uint32_t any_camera16(uint64_t m) {
+    return (uint32_t)((m | (m >> 16) | (m >> 32) | (m >> 48)) & 0xffffull);
+}
+
+template <bool kLds>
+__global__ __launch_bounds__(kBlock, 8) void batched_mark_kernel(
+    const fvv_job* __restrict__ jobs, const JobPrefix* __restrict__ pre,
+    const uint32_t* __restrict__ counter, const fvv_camera* __restrict__ cams,
+    const float* __restrict__ job_pad, const uint32_t* __restrict__ sils,
+    uint8_t* __restrict__ out) {
+    __shared__ uint64_t s_off[kLds ? kBatchedJobLds + 1 : 1];
+    const int nj = (int)counter[2];
+    const auto off = load_offsets<kLds>(pre, nj, s_off);
+    // units one by one while there is a wave for each (a wave then waits for
+    // two classifications), else group by group (most groups are rejected with
+    // one)
+    const uint64_t total = off(nj);
+    const int per = total <= (uint64_t)gridDim.x * kGroup ? 1 : kUnitGroup;
+    const XcdSlice xs = xcd_slice(total / per);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const uint64_t step = (uint64_t)xs.stride * kGroup;
+    uint64_t grp = xs.begin + (uint64_t)xs.slot * kGroup + wave;
+    int jb = 0;
+    if (grp < xs.end)
+        jb = upper_job(off, nj, grp * per);
+    for (; grp < xs.end; grp += step) {
+        const uint64_t unit = grp * per;
+        while (jb + 1 < nj && off(jb + 1) <= unit)   // units ascend
+            ++jb;
+        const int j = __builtin_amdgcn_readfirstlane(jb);
+        const fvv_job& job = jobs[j];
+        const fvv_grid g = job.grid;
+        const JobCams jc = job_cams(job, j, cams, job_pad);
+        const BatchedUnit u = batched_unit(job, (uint32_t)(unit - off(j)));
+        auto rejected = [&](int j0, int rows) {
+            float lo[3], hi[3];
+            box_corners(g, 0, g.dims[0] - 1, j0, min(j0 + rows, g.dims[1]) - 1, u.k0,
+                        min(u.k0 + 4, g.dims[2]) - 1, lo, hi);
+            uint32_t rej, mix;
+            classify_box_wave<kRowRectWords, true>(jc, sils + job.sil_base,
+                                                   (int64_t)jc.H * jc.wpr, lo, hi, rej, mix);
+            return rej != 0u;
+        };
+        if (u.j0 >= g.dims[1] || (per > 1 && rejected(u.j0, kUnitY * kUnitGroup)))
+            continue;
+        for (int q = 0; q < per; ++q) {
+            const int j0 = u.j0 + q * kUnitY;
+            if (j0 >= g.dims[1] || rejected(j0, kUnitY))
+                continue;
+            // its tiles, 16 at a time: lane (b, c) = (tile, camera of four)
+            const int lane = lane_id(), b = lane & 15, cl = lane >> 4;
+            for (int i0 = 16 * b; __ballot(i0 < g.dims[0]) != 0ull; i0 += 256) {
+                float lo[3], hi[3];
+                box_corners(g, min(i0, g.dims[0] - 1), min(i0 + 16, g.dims[0]) - 1, j0,
+                            min(j0 + kUnitY, g.dims[1]) - 1, u.k0, min(u.k0 + 4, g.dims[2]) - 1,
+                            lo, hi);
+                uint32_t live = (uint32_t)(__ballot(i0 < g.dims[0]) & 0xffffull);
+                for (int cb = 0; cb < jc.n && live != 0u; cb += 4) {
+                    const int c = cb + cl;
+                    int cls = kCullMixed;
+                    uint64_t win;
+                    uint32_t org;
+                    if (c < jc.n && ((live >> b) & 1u))
+                        cls = classify_small(jc, c, sils + job.sil_base + (int64_t)c * jc.H * jc.wpr,
+                                             lo, hi, win, org);
+                    live &= ~any_camera16(__ballot(cls == kCullReject));
+                }
+                if (lane < 16 && i0 < g.dims[0])
+                    out[u.at + (int64_t)q * kUnitY * g.dims[0] + i0] =
+                        (live >> b) & 1u ? kLiveMark : kDeadMark;
+            }
+        }
+    }
+}
+
+// A tile of 16 x 16 x 4 samples (from i0, j0, k0) by one wave, without
+// workgroup barriers.  Four cameras at a time:
+//   1. lane (b, c) = (lane % 16, lane / 16) classifies camera cb + c for the
+//      tile's 4 x 4 x 4 sub-block b from its padded corner rectangle, if that
+//      is at most 16 x 32 pixels (else mixed); a mixed rectangle of at most
+//      8 x 8 pixels stays in the lane as a 64-bit window;
+//   2. the mixed (sub-block, camera) pairs of the sub-blocks no camera rejected
+//      are tested with lane = sample, the pixel from the pair's window or,
+//      without one, from the packed rows.
+// Returns in lane b < 16 the occupancy of sub-block b, sample (x, y, z) at bit
+// x + 4 y + 16 z, for the sub-blocks in the mask `sub`, else 0 (the lanes past
+// them hold nothing of use).
+template <class Cams>
+__device__ __forceinline__ uint64_t carve_tile16(const Cams& cams,
+                                                 const uint32_t* __restrict__ sils,
+                                                 const fvv_grid& g, int i0, int j0, int k0,
+                                                 uint32_t sub) {
+    const int lane = lane_id(), b = lane & 15, cl = lane >> 4;
+    const int64_t cam_words = (int64_t)cams.H * cams.wpr;
+    const int nx = g.dims[0], ny = g.dims[1], nz = g.dims[2];
+    const int si = i0 + 4 * (b & 3), sj = j0 + 4 * (b >> 2);
+    const bool sb_on = si < nx && sj < ny && ((sub >> b) & 1u);
+    float lo[3], hi[3];
+    box_corners(g, min(si, nx - 1), min(si + 4, nx) - 1, min(sj, ny - 1), min(sj + 4, ny) - 1, k0,
+                min(k0 + 4, nz) - 1, lo, hi);
+    // sample masks of the sub-block's x, y and z inside the lattice
+    uint64_t occ = 0ull;
+    if (sb_on) {
+        const uint64_t mx = 0xfull >> (4 - min(nx - si, 4)), my = (1ull << (4 * min(ny - sj, 4))) - 1ull;
+        const uint64_t row = (mx * 0x1111ull) & my;
+        const int mz = min(nz - k0, 4);
+        occ = (row * 0x0001000100010001ull) & (~0ull >> (16 * (4 - mz)));
+    }
+    const float Z = lattice_coord(g.lo[2] + k0 + (lane >> 4), g.h, g.origin[2]);
+    for (int cb = 0; cb < cams.n; cb += 4) {
+        const uint32_t live = (uint32_t)(__ballot(occ != 0ull) & 0xffffull);
+        if (live == 0u)
+            break;
+        const int c = cb + cl;
+        int cls = kCullAccept;
+        uint64_t win = 0ull;
+        uint32_t org = kNoWindow;
+        if (c < cams.n && ((live >> b) & 1u))
+            cls = classify_small(cams, c, sils + c * cam_words, lo, hi, win, org);
+        const uint32_t rej = any_camera16(__ballot(cls == kCullReject));
+        if ((rej >> b) & 1u)
+            occ = 0ull;
+        const uint64_t mb = __ballot(cls == kCullMixed);
+        // camera after camera (its matrix stays in scalar registers), its mixed
+        // sub-blocks that are still alive, two at a time (independent chains)
+        for (int q = 0; q < 4; ++q) {
+            uint32_t todo = (uint32_t)(mb >> (16 * q)) & (uint32_t)__ballot(occ != 0ull) & 0xffffu;
+            if (todo == 0u)
+                continue;
+            const int cc = cb + q;
+            float P[12];
+#pragma unroll
+            for (int e = 0; e < 12; ++e)
+                P[e] = cams.Pc(cc)[e];
+            while (todo != 0u) {
+                uint64_t left[2];
+                int sb[2];
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    const int t = __ffs(todo) - 1, src = 16 * q + t;
+                    if (k == 1 || (todo & (todo - 1u)) != 0u)
+                        todo &= todo - 1u;   // (the last one again where there is no second)
+                    sb[k] = t;
+                    const float X = lattice_coord(g.lo[0] + i0 + 4 * (t & 3) + (lane & 3), g.h,
+                                                  g.origin[0]);
+                    const float Y = lattice_coord(g.lo[1] + j0 + 4 * (t >> 2) + ((lane >> 2) & 3),
+                                                  g.h, g.origin[1]);
+                    const uint32_t o = (uint32_t)__builtin_amdgcn_readlane((int)org, src);
+                    const uint64_t w =
+                        ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(win >> 32), src) << 32) |
+                        (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)win, src);
+                    int px, py;
+                    const bool ok = point_pixel_exact(P, X, Y, Z, cams.W, cams.H, px, py);
+                    bool in = (w >> ((8 * (py - (int)(o >> 16)) + px - (int)(o & 0xffffu)) & 63)) & 1ull;
+                    if (o == kNoWindow) {
+                        uint32_t v = 0u;
+                        if (ok)
+                            v = sils[cc * cam_words + (int64_t)py * cams.wpr + (px >> 5)];
+                        in = (v >> (px & 31)) & 1u;
+                    }
+                    left[k] = __ballot(ok && in);
+                }
+#pragma unroll
+                for (int k = 0; k < 2; ++k)
+                    if (lane == sb[k])
+                        occ &= left[k];
+            }
+        }
+    }
+    return occ;
+}
+
+// Four occupancy bits as bytes.
+__device__ __forceinline__ uint32_t nibble_bytes(uint32_t n) {
+    return (n * 0x00204081u) & 0x01010101u;
+}
+
+// The 16 samples along x of row y, layer z of a tile from carve_tile16's
+// lanes: lane = y + 16 z gets bit x.
+__device__ __forceinline__ uint32_t tile16_row(uint64_t occ) {
+    const int lane = lane_id(), y = lane & 15, z = lane >> 4;
+    const int sh = 4 * (y & 3) + 16 * (z & 1);
+    uint32_t bits = 0u;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+        const int src = 4 * (y >> 2) + s;
+        const uint32_t l = (uint32_t)__shfl((int)(uint32_t)occ, src);
+        const uint32_t h = (uint32_t)__shfl((int)(uint32_t)(occ >> 32), src);
+        bits |= (((z >> 1) ? h : l) >> sh & 0xfu) << (4 * s);
+    }
+    return bits;
+}
+
+// Store a row's 16 bytes (the first n of them) at o, at any alignment.
+__device__ __forceinline__ void store_row16(uint8_t* o, uint32_t bits, int n) {
+    uint32_t v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        v[k] = nibble_bytes((bits >> (4 * k)) & 0xfu);
+    if (n >= 16)
+        __builtin_memcpy(o, v, 16);
+    else
+        for (int x = 0; x < n; ++x)
+            o[x] = (uint8_t)((bits >> x) & 1u);
+}
+
+template <bool kLds>
 __global__ __launch_bounds__(kBlock, 6) void carve_batched_culled_kernel(
     const fvv_job* __restrict__ jobs, const JobPrefix* __restrict__ pre,
     const uint32_t* __restrict__ counter, const fvv_camera* __restrict__ cams,
     const float* __restrict__ job_pad, const uint32_t* __restrict__ sils,
     uint8_t* __restrict__ out) {
-    constexpr int TY = kBlock / TX;
-    __shared__ uint64_t s_row_off[kLds ? kBatchedJobLds + 1 : 1];
-    __shared__ int32_t s_tile[kGroup][2];      // rejecting, mixed cameras
+    __shared__ uint64_t s_off[kLds ? kBatchedJobLds + 1 : 1];
+    __shared__ float s_cam[FVV_MAX_CAMS][13];
     const int nj = (int)counter[2];
-    if (kLds)
-        for (int j = threadIdx.x; j <= nj; j += kBlock)
-            s_row_off[j] = pre[j].row_off;
-    __syncthreads();
-    auto off = [&](int m) -> uint64_t {
-        if (kLds)
-            return s_row_off[m];
-        return pre[m].row_off;
-    };
+    const auto off = load_offsets<kLds>(pre, nj, s_off);
     const XcdSlice xs = xcd_slice(off(nj));
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    int jb = 0;
-    if (xs.begin + xs.slot < xs.end)
-        jb = upper_job(off, nj, xs.begin + xs.slot);
-    for (uint64_t row = xs.begin + xs.slot; row < xs.end; row += xs.stride) {
-        // rows ascend, so the job index only moves forward
-        while (jb + 1 < nj && off(jb + 1) <= row)
-            ++jb;
-        const int j = __builtin_amdgcn_readfirstlane(jb);
-        const fvv_job& job = jobs[j];
-        const fvv_grid g = job.grid;
-        const JobCams jc{cams + job.cam_base, job_pad + (int64_t)j * FVV_MAX_CAMS, job.n_cams,
-                         job.width, job.height, (job.width + 31) / 32};
-        const int ntx = (g.dims[0] + TX - 1) / TX;
-        const int nty = (g.dims[1] + TY - 1) / TY;
-        const uint32_t r = (uint32_t)(row - off(j));
-        const int j0 = (int)(r % (uint32_t)nty) * TY, k0 = (int)(r / (uint32_t)nty) * 4;
-        // the whole row first: a camera that rejects the row's box rejects
-        // every tile of it, and the row's TY x 4 sample rows are written as
-        // zeros, each layer's rows one contiguous span
-        __syncthreads();                       // the previous row is done with s_tile
-        if (wave == 0) {
-            float lo[3], hi[3];
-            box_corners(g, 0, g.dims[0] - 1, j0, min(j0 + TY, g.dims[1]) - 1, k0,
-                        min(k0 + 4, g.dims[2]) - 1, lo, hi);
-            uint32_t rej, mix;
-            classify_box_wave<kRowRectWords>(jc, sils + job.sil_base, (int64_t)jc.H * jc.wpr, lo, hi,
-                                         rej, mix);
-            if (lane_id() == 0)
-                s_tile[0][0] = (int32_t)rej;
+    const int lane = lane_id();
+    int staged = -1;
+    // the marks of 64 of the workgroup's units at a time, then the marked ones
+    for (uint64_t base = xs.begin + xs.slot; base < xs.end; base += (uint64_t)xs.stride * kWave) {
+        const uint64_t mine = base + (uint64_t)xs.stride * lane;
+        int jl = 0;
+        bool kept = false;
+        if (mine < xs.end) {
+            jl = upper_job(off, nj, mine);
+            const BatchedUnit u = batched_unit(jobs[jl], (uint32_t)(mine - off(jl)));
+            kept = u.j0 < jobs[jl].grid.dims[1] && out[u.at] >= kDeadMark;
         }
-        __syncthreads();
-        if (__builtin_amdgcn_readfirstlane(s_tile[0][0]) != 0) {
-            const int ny = min(j0 + TY, g.dims[1]) - j0;
-            const int64_t span = (int64_t)ny * g.dims[0];            // bytes per layer
-            const int64_t plane = (int64_t)g.dims[0] * g.dims[1];
-            uint8_t* base = out + job.out_offset + (int64_t)j0 * g.dims[0];
-            for (int z = 0; z < 4 && k0 + z < g.dims[2]; ++z)
-                zero_span(base + (int64_t)(k0 + z) * plane, span);
-            continue;
-        }
-        for (int tx0 = 0; tx0 < ntx; tx0 += kGroup) {
-            __syncthreads();                   // the previous group is done with s_tile
-            if (tx0 + wave < ntx) {
-                uint32_t rej, mix;
-                classify_tile<TX>(jc, sils + job.sil_base, g, (tx0 + wave) * TX, j0, k0, rej,
-                                  mix);
-                if (lane_id() == 0) {
-                    s_tile[wave][0] = (int32_t)rej;
-                    s_tile[wave][1] = (int32_t)mix;
+        uint64_t todo = __ballot(kept);
+        __syncthreads();   // every wave has read the marks, which the carve overwrites
+        for (; todo != 0ull; todo &= todo - 1ull) {
+            const int bit = __ffsll((unsigned long long)todo) - 1;
+            const int j = __builtin_amdgcn_readlane(jl, bit);
+            const fvv_job& job = jobs[j];
+            const fvv_grid g = job.grid;
+            const LdsCams jc{s_cam, job.n_cams, job.width, job.height, (job.width + 31) / 32};
+            const BatchedUnit u =
+                batched_unit(job, (uint32_t)(base + (uint64_t)xs.stride * bit - off(j)));
+            uint8_t* const p = out + u.at;
+            // the job's cameras: a tile reads each several times in a row of
+            // dependent steps
+            if (j != staged) {
+                __syncthreads();   // the previous job's tiles are done with them
+                for (int i = threadIdx.x; i < jc.n * 13; i += kBlock) {
+                    const int c = i / 13, e = i - 13 * c;
+                    s_cam[c][e] = e < 12 ? cams[job.cam_base + c].P[e]
+                                         : job_pad[(int64_t)j * FVV_MAX_CAMS + c];
                 }
+                staged = j;
             }
-            __syncthreads();
-            for (int w = 0; w < kGroup && tx0 + w < ntx; ++w) {
-                // uniform values read back from LDS: scalar registers
-                const uint32_t rej = (uint32_t)__builtin_amdgcn_readfirstlane(s_tile[w][0]);
-                const uint32_t mix = (uint32_t)__builtin_amdgcn_readfirstlane(s_tile[w][1]);
-                carve_tile_culled<TX>(jc, sils + job.sil_base, g, (tx0 + w) * TX, j0, k0,
-                                      out + job.out_offset, RowBits{}, rej != 0, mix);
+            for (int x0 = 0; x0 < g.dims[0]; x0 += 16 * kWave) {
+                // 64 tiles' marks; a dead tile is zero but for its mark
+                const int x = x0 + 16 * lane;
+                const uint8_t mark = x < g.dims[0] ? p[x] : 0;
+                uint64_t live = __ballot(mark == kLiveMark);
+                __syncthreads();   // every wave has read the marks; the cameras are staged
+                if (wave == 0 && mark == kDeadMark)
+                    p[x] = 0;
+                // a tile per wave; one or two tiles are shared out in 4 or 2
+                // parts of 4 or 8 rows (the waves would idle)
+                const int nl = __popcll(live);
+                const int parts = nl == 1 ? 4 : nl == 2 ? 2 : 1, rows = 16 / parts;
+                const int part = wave % parts;
+                const uint32_t sub = parts == 1 ? 0xffffu : ((1u << rows) - 1u) << (part * rows);
+                for (int q = 0; live != 0ull; live &= live - 1ull, ++q) {
+                    if (q % (kGroup / parts) != wave / parts)
+                        continue;
+                    const int i0 = x0 + 16 * (__ffsll((unsigned long long)live) - 1);
+                    const uint32_t row =
+                        tile16_row(carve_tile16(jc, sils + job.sil_base, g, i0, u.j0, u.k0, sub));
+                    const int y = lane & 15, z = lane >> 4;
+                    if (u.j0 + y < g.dims[1] && u.k0 + z < g.dims[2] && y / rows == part)
+                        store_row16(p + ((int64_t)z * g.dims[1] + y) * g.dims[0] + i0, row,
+                                    min(16, g.dims[0] - i0));
+                }
             }
         }
     }
@@ -1936,28 +2276,38 @@ hipError_t launch_carve_batched(fvv_ctx* ctx, const fvv_job* jobs, uint32_t n_jo
                                 hipStream_t s) {
     // a fresh job table carved without fine bitmaps, 4 samples deep: culled
     if (!jobs_prepared && !finebits && t.tz == 4) {
-        blocks = (blocks + kXcds - 1) / kXcds * kXcds;
+        // workgroups for the marked units: 32 per CU (8, 16, 32 and 64 take
+        // 840, 812, 803 and 825 us on 64 frames x 12 ROIs), fewer for a small
+        // table (1000 workgroups take 1 us to start)
+        const uint64_t most = (uint64_t)ctx->n_cus * 32;
+        uint64_t want = (uint64_t)n_jobs * 32;
+        want = want < most / 4 ? most / 4 : want > most ? most : want;
+        blocks = (int)((want + kXcds - 1) / kXcds * kXcds);
         const uint64_t pairs = (uint64_t)n_jobs * FVV_MAX_CAMS;
-        hipLaunchKernelGGL(job_pad_kernel, dim3((unsigned)((pairs + kBlock - 1) / kBlock)),
-                           dim3(kBlock), 0, s, jobs, n_jobs, cams, ctx->d_job_pad);
-#define X(TXV)                                                                                 \
-        if (t.tx == TXV) {                                                                     \
-            hipLaunchKernelGGL((batched_prepare_kernel<TXV, 4>), dim3(1), dim3(kBlock), 0, s,  \
-                               jobs, n_jobs, ctx->d_prefix, ctx->d_counter, ctx->d_status,     \
-                               (uint32_t)blocks);                                              \
-            if (n_jobs <= (uint32_t)kBatchedJobLds)                                           \
-                hipLaunchKernelGGL((carve_batched_culled_kernel<TXV, true>), dim3(blocks),     \
-                                   dim3(kBlock), 0, s, jobs, ctx->d_prefix, ctx->d_counter,    \
-                                   cams, ctx->d_job_pad, sils, out);                           \
-            else                                                                               \
-                hipLaunchKernelGGL((carve_batched_culled_kernel<TXV, false>), dim3(blocks),    \
-                                   dim3(kBlock), 0, s, jobs, ctx->d_prefix, ctx->d_counter,    \
-                                   cams, ctx->d_job_pad, sils, out);                           \
-            return hipGetLastError();                                                          \
+        // the first two passes' waves stay resident: eight workgroups per CU
+        const unsigned rblocks = (unsigned)((ctx->n_cus * 8 + kXcds - 1) / kXcds * kXcds);
+        const unsigned pad_blocks = (unsigned)((pairs + kBlock - 1) / kBlock);
+        // at least about 16 zeroing workgroups per CU
+        const unsigned parts = ((unsigned)ctx->n_cus * 16 + n_jobs - 1) / n_jobs;
+        hipLaunchKernelGGL(batched_zero_kernel, dim3(1 + pad_blocks + n_jobs * parts),
+                           dim3(kBlock), 0, s, jobs, n_jobs, cams, ctx->d_job_pad, ctx->d_prefix,
+                           ctx->d_counter, ctx->d_status, pad_blocks, parts, out);
+        if (n_jobs <= (uint32_t)kBatchedJobLds) {
+            hipLaunchKernelGGL((batched_mark_kernel<true>), dim3(rblocks), dim3(kBlock), 0, s,
+                               jobs, ctx->d_prefix, ctx->d_counter, cams, ctx->d_job_pad, sils,
+                               out);
+            hipLaunchKernelGGL((carve_batched_culled_kernel<true>), dim3(blocks), dim3(kBlock), 0,
+                               s, jobs, ctx->d_prefix, ctx->d_counter, cams, ctx->d_job_pad, sils,
+                               out);
+        } else {
+            hipLaunchKernelGGL((batched_mark_kernel<false>), dim3(rblocks), dim3(kBlock), 0, s,
+                               jobs, ctx->d_prefix, ctx->d_counter, cams, ctx->d_job_pad, sils,
+                               out);
+            hipLaunchKernelGGL((carve_batched_culled_kernel<false>), dim3(blocks), dim3(kBlock),
+                               0, s, jobs, ctx->d_prefix, ctx->d_counter, cams, ctx->d_job_pad,
+                               sils, out);
         }
-        X(64) X(32) X(16)
-#undef X
-        return hipErrorInvalidValue;
+        return hipGetLastError();
     }
 #define X(TXV, TZV)                                                                             \
     if (t.tx == TXV && t.tz == TZV) {                                                           \

@@ -458,9 +458,8 @@ constexpr int kStatsRow = 8;   // per component: count, lo[3], hi[3], smallest l
 // Per job of a batched carve / surface: first carving tile and first
 // crossing-edge work item (exclusive prefix sums over the job table).
 struct JobPrefix {
-    uint64_t tile_off;   // first tile of the job
+    uint64_t tile_off;   // first tile of the job (culled batched carve: first unit)
     uint64_t bit_off;    // first word of the job's fine bitmap
-    uint64_t row_off;    // first tile row (tiles sharing y and z) of the job (batched carve)
     uint32_t item_off;   // first crossing-edge work item of the job
     uint32_t pad;
 };
