@@ -1586,8 +1586,7 @@ __global__ __launch_bounds__(kBlock, 7) void carve_frame_kernel(const fvv_job* _
     if (blockIdx.x >= lw.carve_blocks) {
         const int64_t stride = (int64_t)(gridDim.x - lw.carve_blocks) * kBlock;
         const int64_t t0 = (int64_t)(blockIdx.x - lw.carve_blocks) * kBlock + threadIdx.x;
-        for (int64_t v = t0; v < lw.V; v += stride)
-            label_write_sample(lw, v);
+        label_write_samples(lw, t0, stride);
         label_write_clear(lw, t0, stride);
         return;
     }
@@ -2177,12 +2176,14 @@ hipError_t launch_carve_frame(fvv_ctx* ctx, const fvv_job* jobs, int max_jobs,
         return e;
     }
     blocks = (blocks + kXcds - 1) / kXcds * kXcds;
-    // the coarse labels' write pass rides in the same launch, about eight
-    // samples per thread in workgroups after the carve's
+    // the coarse labels' write pass rides in the same launch, in workgroups
+    // after the carve's: eight samples or more per thread, at most 16
+    // workgroups per CU (2.3e7 samples: 58, 48, 40, 40, 41 us with 1, 2, 8, 16
+    // and 32; 40 to 45 with them first)
     LabelWrite lw = label_write_args(ctx, coarse, occ_coarse, labels);
     lw.carve_blocks = (uint32_t)blocks;
     const int64_t lw_blocks = (lw.V + 8 * kBlock - 1) / (8 * kBlock);
-    const int extra = (int)(lw_blocks < 1 ? 1 : (lw_blocks > 4 * ctx->n_cus ? 4 * ctx->n_cus
+    const int extra = (int)(lw_blocks < 1 ? 1 : (lw_blocks > 16 * ctx->n_cus ? 16 * ctx->n_cus
                                                                               : lw_blocks));
     // jobs: max_jobs entries; the prefix table holds at least max_jobs + 1
     const int job_lds = max_jobs < kJobLds ? max_jobs : kJobLds;

@@ -768,12 +768,18 @@ __global__ __launch_bounds__(kBlock) void label_bitmap_kernel(const uint8_t* __r
     }
 }
 
+// kWide: four samples at a time; else one sample per thread.
+template <bool kWide>
 __global__ __launch_bounds__(kBlock) void label_write_kernel(const LabelWrite lw) {
     const int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     label_write_clear(lw, v, (int64_t)gridDim.x * kBlock);
-    if (v < lw.V)
+    if (kWide)
+        label_write_samples(lw, v, (int64_t)gridDim.x * kBlock);
+    else if (v < lw.V)
         label_write_sample(lw, v);
 }
+
+constexpr int64_t kWideLabels = (int64_t)1 << 22;
 
 LabelWrite label_write_args(fvv_ctx* ctx, const fvv_grid& g, uint8_t* occ, int32_t* labels) {
     LabelWrite lw;
@@ -835,8 +841,14 @@ hipError_t launch_label(fvv_ctx* ctx, const fvv_grid& g, uint8_t* occ, int32_t* 
 hipError_t launch_label_write(fvv_ctx* ctx, const fvv_grid& g, uint8_t* occ, int32_t* labels,
                               hipStream_t s) {
     const LabelWrite lw = label_write_args(ctx, g, occ, labels);
-    const unsigned vblocks = (unsigned)((lw.V + kBlock - 1) / kBlock);
-    hipLaunchKernelGGL(label_write_kernel, dim3(vblocks), dim3(kBlock), 0, s, lw);
+    // a small lattice's pass is as long as one thread's chain, which is shorter
+    // for one sample (the calls around 1e6 samples: 54.9 against 55.8 us)
+    if (lw.V < kWideLabels)
+        hipLaunchKernelGGL(label_write_kernel<false>,
+                           dim3((unsigned)((lw.V + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, lw);
+    else
+        hipLaunchKernelGGL(label_write_kernel<true>, dim3((unsigned)ctx->n_cus * 8), dim3(kBlock),
+                           0, s, lw);
     return hipGetLastError();
 }
 
