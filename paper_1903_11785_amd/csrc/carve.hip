@@ -1327,6 +1327,26 @@ __device__ __forceinline__ uint64_t tiled_window(const uint64_t* __restrict__ tc
     return ((t0 >> ox) & lo) | (ox ? (t1 << (8 - ox)) & ~lo : 0ull);
 }
 
+// Wave-uniform values read from LDS, into scalar registers.
+__device__ __forceinline__ int32_t uniform(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ float uniform(float v) {
+    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
+}
+__device__ __forceinline__ uint64_t uniform(uint64_t v) {
+    return ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32)) << 32) |
+           (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+}
+__device__ __forceinline__ fvv_grid uniform(const fvv_grid& v) {
+    fvv_grid g;
+    for (int a = 0; a < 3; ++a) {
+        g.origin[a] = uniform(v.origin[a]);
+        g.lo[a] = uniform(v.lo[a]);
+        g.dims[a] = uniform(v.dims[a]);
+    }
+    g.h = uniform(v.h);
+    return g;
+}
+
 // A (sub-block, camera) pair's window as the tests read it: the pixels, and
 // the window's corner pixel (x | y << 16), or kNoWindow when the camera's
 // rectangle is larger than 8 x 8 pixels (its tests then load packed words).
@@ -1361,10 +1381,15 @@ struct PairWindow {
 //   3. output: the occupancy bytes, and the block's 16 bits of each fine-bitmap
 //      row word.
 // cam_lds: per camera P and the rounding pad; rho: the job's radii per camera
-// (kRhoPer floats); win: this wave's LDS windows [4][FVV_MAX_CAMS].  Returns
+// (kRhoPer floats); win: this wave's LDS windows [4][FVV_MAX_CAMS].  kSome:
+// only n_sel cameras are left to look at, number r in lane r's `sel`, the
+// others accept every sample of the block; and the output is zero before, so
+// that an empty block writes nothing.  Returns
 // the number of test passes, and in the high half the (sub-block, camera)
 // tests they made (wave-uniform counts, for measurement builds).
-__device__ __forceinline__ uint32_t carve_block16(const CamSet& cams, const float (*cam_lds)[13],
+template <bool kSome>
+__device__ __forceinline__ uint32_t carve_block16(const CamSet& cams, int n_sel, int sel,
+                                                  const float (*cam_lds)[13],
                                               const float* __restrict__ rho,
                                               PairWindow (*win)[FVV_MAX_CAMS],
                                               const uint32_t* __restrict__ sils,
@@ -1391,10 +1416,13 @@ __device__ __forceinline__ uint32_t carve_block16(const CamSet& cams, const floa
         const float Xc = 0.5f * (lo[0] + hi[0]), Yc = 0.5f * (lo[1] + hi[1]);
         const float Zc = 0.5f * (lo[2] + hi[2]);
         uint32_t rej[4] = {0u, 0u, 0u, 0u}, mix[4] = {0u, 0u, 0u, 0u};
-        for (int cb = 0; cb < cams.n; cb += 16) {
+        const int n_look = kSome ? n_sel : cams.n;
+        for (int cb = 0; cb < n_look; cb += 16) {
+            // c: the camera (kSome: its number among those left)
             const int c = cb + cl;
-            const bool on = sb_on && c < cams.n;
-            const int cc = on ? c : 0;
+            const bool on = sb_on && c < n_look;
+            const int named = kSome ? __shfl(sel, c & 63) : c;   // (from every lane)
+            const int cc = on ? named : 0;
             const float* P = cam_lds[cc];
             const float rx = rho[cc * kRhoPer + 0], ry = rho[cc * kRhoPer + 1];
             const float a = __builtin_fmaf(P[2], Zc, __builtin_fmaf(P[1], Yc, __builtin_fmaf(P[0], Xc, P[3])));
@@ -1452,6 +1480,10 @@ __device__ __forceinline__ uint32_t carve_block16(const CamSet& cams, const floa
                 rej[s] |= (uint32_t)(rb >> (16 * s)) & 0xffffu;
                 mix[s] |= ((uint32_t)(mb >> (16 * s)) & 0xffffu) << cb;
             }
+            // no sub-block left for the next cameras
+            if (cb + 16 < n_look && rej[0] != 0u && (rej[1] != 0u || bi0 + 4 >= nx) &&
+                (rej[2] != 0u || bi0 + 8 >= nx) && (rej[3] != 0u || bi0 + 12 >= nx))
+                break;
         }
         wave_lds_sync();   // the windows, written above, are read below by every lane
         // 2. tests
@@ -1482,14 +1514,15 @@ __device__ __forceinline__ uint32_t carve_block16(const CamSet& cams, const floa
                     const int c = __ffs(rest[s]) - 1;
                     rest[s] &= rest[s] - 1u;
                     const PairWindow pw = win[s][c];
+                    const int cam = kSome ? __builtin_amdgcn_readlane(sel, c) : c;
                     org[s] = (uint32_t)__builtin_amdgcn_readfirstlane((int)pw.org);
                     wbits[s] = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(pw.bits >> 32)) << 32) |
                                (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)pw.bits);
-                    ok[s] = point_pixel_exact(cams.Pc(c), X[s], Y, Z, cams.W, cams.H, px[s],
+                    ok[s] = point_pixel_exact(cams.Pc(cam), X[s], Y, Z, cams.W, cams.H, px[s],
                                               py[s]);
                     word[s] = 0u;
                     if (org[s] == kNoWindow && ok[s])
-                        word[s] = sils[c * cam_words + py[s] * cams.wpr + (px[s] >> 5)];
+                        word[s] = sils[cam * cam_words + py[s] * cams.wpr + (px[s] >> 5)];
                 }
             }
 #pragma unroll
@@ -1513,6 +1546,8 @@ __device__ __forceinline__ uint32_t carve_block16(const CamSet& cams, const floa
             occ[s] = __ballot(alive[s]);
         wave_lds_sync();   // the next block rewrites the windows
     }
+    if (kSome && (occ[0] | occ[1] | occ[2] | occ[3]) == 0ull)
+        return n_pass | (n_test << 16);
     // 3. output: bytes, lane -> (x, y) = (lane % 16, lane / 16), every z
     const uint64_t plane = (uint64_t)nx * (uint64_t)ny;
     {
@@ -1546,6 +1581,118 @@ __device__ __forceinline__ uint32_t carve_block16(const CamSet& cams, const floa
     return n_pass | (n_test << 16);
 }
 
+// A brick: kFineBrickX x kFineBrickYZ x kFineBrickYZ samples, four blocks.
+constexpr int kFineBrickX = 16, kFineBrickYZ = 8;
+
+// Classification of every camera for two bricks side by side along x (the first
+// one's first sample i0, j0, k0) by one wave, lane = (brick l / 32, camera l %
+// 32; four bricks of 16 lanes for rigs of up to 16 cameras, compiled in beside
+// it, spilled registers): the rectangle around
+// the rcp quotient of the brick's centre, its half-widths the sums of the job's
+// edge radii (each of half a spacing, so 15, 7 and 7 of them span the brick's
+// half-extents), as in carve_block16; read from up to 4 x 4 tiled blocks
+// (larger: mixed).  Returns the ballot of the cameras that reject every sample
+// of their brick, and in mixed that of those that neither reject nor accept all
+// of them (bricks past the lattice have neither).
+__device__ __forceinline__ uint64_t classify_bricks(const CamSet& cams, const float (*cam_lds)[13],
+                                                    const float* __restrict__ rho,
+                                                    const uint64_t* __restrict__ tiles, int tpr,
+                                                    int64_t tpc, const fvv_grid& g, int i0, int j0,
+                                                    int k0, uint64_t& mixed) {
+    const int lane = lane_id(), ib = i0 + (lane >> 5) * kFineBrickX;
+    const bool on = (lane & 31) < cams.n && ib < g.dims[0];
+    const int c = on ? lane & 31 : 0;
+    float lo[3], hi[3];
+    box_corners(g, min(ib, g.dims[0] - 1), min(ib + kFineBrickX, g.dims[0]) - 1, j0,
+                min(j0 + kFineBrickYZ, g.dims[1]) - 1, k0, min(k0 + kFineBrickYZ, g.dims[2]) - 1, lo, hi);
+    const float Xc = 0.5f * (lo[0] + hi[0]), Yc = 0.5f * (lo[1] + hi[1]);
+    const float Zc = 0.5f * (lo[2] + hi[2]);
+    const float* P = cam_lds[c];
+    const float* r = rho + c * kRhoPer;
+    constexpr float ex = kFineBrickX - 1, eyz = kFineBrickYZ - 1;
+    const float rx = ex * r[2] + eyz * (r[4] + r[6]), ry = ex * r[3] + eyz * (r[5] + r[7]);
+    const float a = __builtin_fmaf(P[2], Zc, __builtin_fmaf(P[1], Yc, __builtin_fmaf(P[0], Xc, P[3])));
+    const float b = __builtin_fmaf(P[6], Zc, __builtin_fmaf(P[5], Yc, __builtin_fmaf(P[4], Xc, P[7])));
+    const float w = __builtin_fmaf(P[10], Zc, __builtin_fmaf(P[9], Yc, __builtin_fmaf(P[8], Xc, P[11])));
+    const float q = __builtin_amdgcn_rcpf(w);
+    const float W = (float)cams.W, H = (float)cams.H;
+    const bool bounded = rx < 32.0f && ry < 32.0f;   // (wider: more than 4 blocks)
+    const float sx = bounded ? rx : 0.0f, sy = bounded ? ry : 0.0f;
+    const float qa = __builtin_amdgcn_fmed3f(a * q, -64.0f, W + 64.0f);
+    const float qb = __builtin_amdgcn_fmed3f(b * q, -64.0f, H + 64.0f);
+    const int x0 = (int)__builtin_floorf(qa - sx), x1 = (int)__builtin_floorf(qa + sx);
+    const int y0 = (int)__builtin_floorf(qb - sy), y1 = (int)__builtin_floorf(qb + sy);
+    const bool inside = x0 >= 0 && y0 >= 0 && x1 < cams.W && y1 < cams.H;
+    const int cx0 = max(x0, 0), cx1 = min(x1, cams.W - 1);
+    const int cy0 = max(y0, 0), cy1 = min(y1, cams.H - 1);
+    const bool off = cx0 > cx1 || cy0 > cy1;
+    const int bx0 = cx0 >> 3, by0 = cy0 >> 3, nbx = (cx1 >> 3) - bx0, nby = (cy1 >> 3) - by0;
+    const bool known = on && bounded && !off && nbx < 4 && nby < 4;
+    bool any = false, all = true;
+    if (known) {
+        const uint64_t* t = tiles + c * tpc + (int64_t)by0 * tpr + bx0;
+        uint64_t cols[4];
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            const int x = 8 * (bx0 + d), c0 = max(cx0 - x, 0), c1 = max(min(cx1 - x, 7), 0);
+            cols[d] = d <= nbx ? (uint64_t)((2u << c1) - (1u << c0)) * 0x0101010101010101ull : 0ull;
+        }
+        // (a block row at a time: all sixteen blocks at once spill registers)
+#pragma unroll 1
+        for (int e = 0; e <= nby; ++e) {
+            const int y = 8 * (by0 + e), r0 = max(cy0 - y, 0), r1 = min(cy1 - y, 7);
+            const uint64_t rows = (~0ull >> (8 * (7 - r1))) & (~0ull << (8 * r0));
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                const uint64_t m = cols[d] & rows;
+                const uint64_t v = t[(int64_t)e * tpr + min(d, nbx)];
+                any |= (v & m) != 0ull;
+                all &= (v & m) == m;
+            }
+        }
+    }
+    const bool rej = on && bounded && (off || (known && !any));
+    mixed = __ballot(on && !rej && !(known && inside && all));
+    return __ballot(rej);
+}
+
+// A brick whose samples are all occupied: its occupancy bytes and its 16 bits of
+// each fine-bitmap row word (the bits past nx clear), lane = row (y, z) = (l % 8,
+// l / 8).
+__device__ __forceinline__ void fill_brick(const fvv_grid& g, int i0, int j0, int k0,
+                                           uint8_t* __restrict__ out, const RowBits& fb) {
+    const int lane = lane_id(), j = j0 + (lane & 7), k = k0 + (lane >> 3);
+    if (j >= g.dims[1] || k >= g.dims[2])
+        return;
+    const int64_t row = (int64_t)j + (int64_t)g.dims[1] * k;
+    const int n = min(g.dims[0] - i0, 16);
+    uint8_t* o = out + row * g.dims[0] + i0;
+    const uint32_t v[4] = {0x01010101u, 0x01010101u, 0x01010101u, 0x01010101u};
+    if (n == 16)
+        __builtin_memcpy(o, v, 16);
+    else
+        for (int x = 0; x < n; ++x)
+            o[x] = 1;
+    reinterpret_cast<uint16_t*>(fb.words + row * fb.wr + (i0 >> 6))[(i0 & 63) >> 4] =
+        (uint16_t)((1u << n) - 1u);
+}
+
+// Zero n bytes from p by one wave: 16-byte stores between the first and the
+// last 16-byte boundary, byte stores at the ends.
+__device__ __forceinline__ void wave_zero_span(uint8_t* p, int64_t n) {
+    const int lane = lane_id();
+    const int64_t head = (int64_t)((16 - ((uintptr_t)p & 15)) & 15);
+    const int64_t h = head < n ? head : n;
+    const int64_t n16 = (n - h) / 16, tail0 = h + 16 * n16;
+    uint4* q = reinterpret_cast<uint4*>(p + h);
+    for (int64_t i = lane; i < n16; i += kWave)
+        q[i] = make_uint4(0u, 0u, 0u, 0u);
+    if (lane < h)
+        p[lane] = 0;
+    if (lane < n - tail0)
+        p[tail0 + lane] = 0;
+}
+
 // Measurement builds (FVV_CARVE_PROBE defined) record, for the first
 // kProbeWaves waves of the frame's fine carve, the real-time clock (100 MHz)
 // at the wave's entry and exit, its block count and the time its workgroup's
@@ -1567,7 +1714,45 @@ __device__ uint64_t carve_probe_waves[kProbeWaves][3];
 // 16 (w mod TX/16), y offset 4 (w div TX/16)) and carves it on its own, with
 // no workgroup barrier (carve_block16).  Job tables of up to kJobLds ROIs and
 // the cameras' matrices and rounding pads are kept in LDS.
+//
+// A large frame (at least kGroupTiles tiles of 1024 samples, its jobs in LDS)
+// goes by groups of bricks side by side along x instead: most of its blocks lie
+// well outside or inside, and 16-byte pieces of rows are what its time goes to.
+// A workgroup zeroes a group's output while it classifies the cameras for the
+// bricks; the bricks that no camera rejects go into a list in LDS, from which
+// the waves take one block after the other (carve_block16 for the brick's mixed
+// cameras) or a whole brick to fill.  From kWideGroupTiles on a group spans up
+// to 64 bricks (whole rows: each layer's zeros are one span); below, 8, so that
+// there are several groups per workgroup.  4.3e8 samples in 24 cameras: 1500 us
+// by tiles, 850 by bricks each written on its own (680 of them for the writes
+// alone), 380 by groups; whole frames of 8, 13, 24, 28 and 30e6 samples (16 to
+// 24 cameras) 176, 285, 298, 330 and 297 us against 176, 298, 330, 353 and 367.
+// Smaller ones lose by it (5e6 samples of 56 ROIs: 267 against 255, a frame of
+// 4e6: the carve 49 against 42).
 constexpr int kJobLds = 64;
+constexpr int kGroupBricks = 64;
+constexpr uint64_t kGroupTiles = 12288, kWideGroupTiles = 65536;
+
+// A group: `bricks` bricks side by side along x.  What is left of it: the bricks
+// that no camera rejects, by place along x and mixed cameras (none: all full),
+// their count and the next block to take, of this group and of the next (par:
+// whose turn); and the group itself, read back per block so that the block loop
+// keeps little of it in registers (kept in scalar registers, it spilled a
+// hundred of them).
+struct GroupList {
+    uint16_t brick[kGroupBricks];
+    uint32_t mixed[kGroupBricks];
+    uint32_t left[2], next[2];
+    uint64_t t;
+    int32_t jb, i0, j0, k0, par;
+};
+
+__device__ __forceinline__ uint64_t fine_groups(const fvv_grid& g, int bricks) {
+    const int x = bricks * kFineBrickX;
+    return (uint64_t)((g.dims[0] + x - 1) / x) *
+           (uint64_t)((g.dims[1] + kFineBrickYZ - 1) / kFineBrickYZ) *
+           (uint64_t)((g.dims[2] + kFineBrickYZ - 1) / kFineBrickYZ);
+}
 
 template <int TX>
 __global__ __launch_bounds__(kBlock, 7) void carve_frame_kernel(const fvv_job* __restrict__ jobs,
@@ -1601,6 +1786,7 @@ __global__ __launch_bounds__(kBlock, 7) void carve_frame_kernel(const fvv_job* _
     __shared__ int64_t s_out[kJobLds];
     __shared__ fvv_grid s_grid[kJobLds];
     __shared__ float s_cam[FVV_MAX_CAMS][13];        // P, then the rounding pad
+    __shared__ GroupList s_list;
     // the job tables of the first job_lds jobs (every job the output can hold,
     // up to kJobLds), loaded without waiting for the frame's job count
     for (int j = threadIdx.x; j <= job_lds; j += kBlock) {
@@ -1661,7 +1847,8 @@ __global__ __launch_bounds__(kBlock, 7) void carve_frame_kernel(const fvv_job* _
         const uint64_t t_a = __builtin_amdgcn_s_memrealtime();
 #endif
         const uint32_t passes_tests =
-            carve_block16(cams, s_cam, rho + (int64_t)jb * FVV_MAX_CAMS * kRhoPer, s_win[wave],
+            carve_block16<false>(cams, 0, 0, s_cam, rho + (int64_t)jb * FVV_MAX_CAMS * kRhoPer,
+                                 s_win[wave],
                           sils, tiles, tpr, tpc, g, i0 + xo, j0 + yo, k0, out + out_off, fb);
 #ifdef FVV_CARVE_PROBE
         const uint64_t t_b = __builtin_amdgcn_s_memrealtime();
@@ -1678,10 +1865,134 @@ __global__ __launch_bounds__(kBlock, 7) void carve_frame_kernel(const fvv_job* _
 #endif
     }
     };
-    if (lds)
+    if (lds && s_tile_off[nj] >= kGroupTiles) {
+        // the groups' prefix over the jobs, in the tiles' place
+        const int bricks = s_tile_off[nj] >= kWideGroupTiles ? kGroupBricks : 8;
+        __syncthreads();
+        if (threadIdx.x < kWave) {
+            const uint64_t n = (int)threadIdx.x < nj ? fine_groups(s_grid[threadIdx.x], bricks) : 0ull;
+            const uint64_t inc = wave_inclusive_sum64(n);
+            if ((int)threadIdx.x < nj)
+                s_tile_off[threadIdx.x + 1] = inc;
+            if (threadIdx.x == 0) {
+                s_tile_off[0] = 0ull;
+                s_list.left[0] = s_list.next[0] = 0u;
+            }
+        }
+        __syncthreads();
+        GroupList& list = s_list;
+        const int lane = lane_id();
+        uint64_t t = blockIdx.x;
+        int par = 0;
+        while (t < uniform(s_tile_off[nj])) {
+            // 1. the group's output zeroed, and the cameras classified for its
+            // bricks, two per wave at once
+            {
+                const int jb = uniform(upper_job([&](int m) { return s_tile_off[m]; }, nj, t));
+                const fvv_grid g = uniform(s_grid[jb]);
+                const uint64_t q = t - uniform(s_tile_off[jb]);
+                const uint32_t ngx = (uint32_t)((g.dims[0] + bricks * kFineBrickX - 1) /
+                                                (bricks * kFineBrickX));
+                const uint32_t ngy = (uint32_t)((g.dims[1] + kFineBrickYZ - 1) / kFineBrickYZ);
+                const uint64_t qy = q / ngx;
+                const int i0 = (int)(q - qy * ngx) * bricks * kFineBrickX;
+                const int j0 = (int)(qy % ngy) * kFineBrickYZ, k0 = (int)(qy / ngy) * kFineBrickYZ;
+                {
+                    const int nr = min(kFineBrickYZ, g.dims[1] - j0);
+                    const int rows = nr * min(kFineBrickYZ, g.dims[2] - k0);
+                    const int n = min(g.dims[0] - i0, bricks * kFineBrickX);
+                    const int wr = (g.dims[0] + 63) / 64, np = (n + 15) / 16, nw = (n + 63) / 64;
+                    uint8_t* const o = out + uniform((uint64_t)s_out[jb]) + i0;
+                    uint64_t* const words = finebits + uniform(s_bit_off[jb]) + (i0 >> 6);
+                    const uint32_t z[4] = {0u, 0u, 0u, 0u};
+                    if (n == g.dims[0]) {      // whole rows: one span per layer
+                        for (int l = wave; l * nr < rows; l += kBlock / kWave)
+                            wave_zero_span(o + ((int64_t)j0 + (int64_t)g.dims[1] * (k0 + l)) * n,
+                                           (int64_t)nr * n);
+                    } else for (int e = threadIdx.x; e < rows * np; e += kBlock) {
+                        const int rw = e / np, x = 16 * (e - rw * np);
+                        const int64_t row = (int64_t)(j0 + rw % nr) + (int64_t)g.dims[1] * (k0 + rw / nr);
+                        uint8_t* const p = o + row * g.dims[0] + x;
+                        if (x + 16 <= n)
+                            __builtin_memcpy(p, z, 16);
+                        else
+                            for (int b = 0; b < n - x; ++b)
+                                p[b] = 0;
+                    }
+                    for (int e = threadIdx.x; e < rows * nw; e += kBlock) {
+                        const int rw = e / nw;
+                        const int64_t row = (int64_t)(j0 + rw % nr) + (int64_t)g.dims[1] * (k0 + rw / nr);
+                        words[row * wr + (e - rw * nw)] = 0ull;
+                    }
+                }
+                const int nb = min((g.dims[0] - i0 + kFineBrickX - 1) / kFineBrickX, bricks);
+                for (int b0 = 2 * wave; b0 < nb; b0 += 2 * (kBlock / kWave)) {
+                    uint64_t mixed;
+                    const uint64_t rej =
+                        classify_bricks(cams, s_cam, rho + (int64_t)jb * FVV_MAX_CAMS * kRhoPer,
+                                        tiles, tpr, tpc, g, i0 + b0 * kFineBrickX, j0, k0, mixed);
+                    const int b = lane >> 5;
+                    if ((lane & 31) == 0 && b0 + b < nb && (uint32_t)(rej >> (32 * b)) == 0u) {
+                        const uint32_t at = atomicAdd(&list.left[par], 1u);
+                        list.brick[at] = (uint16_t)(b0 + b);
+                        list.mixed[at] = (uint32_t)(mixed >> (32 * b));
+                    }
+                }
+                if (threadIdx.x == 0) {
+                    list.t = t;
+                    list.jb = jb;
+                    list.i0 = i0;
+                    list.j0 = j0;
+                    list.k0 = k0;
+                    list.par = par;
+                    list.left[par ^ 1] = list.next[par ^ 1] = 0u;
+                }
+            }
+            __syncthreads();           // the list is complete, the zeros are written
+            // 2. the blocks of the bricks that no camera rejects, one after the
+            // other by whichever wave is free
+            for (;;) {
+                const int p = uniform(list.par);
+                uint32_t item = 0u;
+                if (lane == 0)
+                    item = atomicAdd(&list.next[p], 1u);
+                item = (uint32_t)uniform((int)item);
+                if (item >= 4u * (uint32_t)uniform((int)list.left[p]))
+                    break;
+                const int jb = uniform(list.jb);
+                const fvv_grid g = uniform(s_grid[jb]);
+                const int i0 = uniform(list.i0) + kFineBrickX * uniform((int)list.brick[item >> 2]);
+                const uint32_t mix = (uint32_t)uniform((int)list.mixed[item >> 2]);
+                const int j0 = uniform(list.j0), k0 = uniform(list.k0), b = (int)(item & 3u);
+                const int jy = j0 + 4 * (b & 1), kz = k0 + 4 * (b >> 1);
+                RowBits fb{};
+                fb.words = finebits + uniform(s_bit_off[jb]);
+                fb.wr = (g.dims[0] + 63) / 64;
+                uint8_t* const o = out + uniform((uint64_t)s_out[jb]);
+                if (mix == 0u) {
+                    if (b == 0)
+                        fill_brick(g, i0, j0, k0, o, fb);
+                    continue;
+                }
+                if (jy >= g.dims[1] || kz >= g.dims[2])
+                    continue;
+                // lane r: the r-th mixed camera
+                const int rank = __popc(mix & (uint32_t)lanes_below_mask());
+                const int sel = __builtin_amdgcn_ds_permute(
+                    4 * (lane < 32 && ((mix >> (lane & 31)) & 1u) ? rank : 63), lane);
+                carve_block16<true>(cams, __popc(mix), sel, s_cam,
+                                    rho + (int64_t)jb * FVV_MAX_CAMS * kRhoPer, s_win[wave], sils,
+                                    tiles, tpr, tpc, g, i0, jy, kz, o, fb);
+            }
+            t = uniform(list.t) + lw.carve_blocks;
+            par = uniform(list.par) ^ 1;
+            __syncthreads();           // the list is free
+        }
+    } else if (lds) {
         tiles_loop(std::true_type{});
-    else
+    } else {
         tiles_loop(std::false_type{});
+    }
 #ifdef FVV_CARVE_PROBE
     const uint32_t pw = blockIdx.x * (kBlock / kWave) + wave;
     if (lane_id() == 0 && pw < (uint32_t)kProbeWaves) {
