@@ -1804,13 +1804,25 @@ __global__ __launch_bounds__(kBlock, 7) void carve_frame_kernel(const fvv_job* _
         s_cam[c][e] = e < 12 ? cams.P[c][e] : cams.pad[c];
     }
     __syncthreads();
-#ifdef FVV_CARVE_PROBE
-    const uint64_t probe_tables = __builtin_amdgcn_s_memrealtime();
-#endif
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int xo = 16 * (wave % BXN), yo = 4 * (wave / BXN);
     const int tpr = (cams.W + 7) / 8;
     const int64_t tpc = (int64_t)tpr * ((cams.H + 7) / 8);
+#ifdef FVV_CARVE_PROBE
+    const uint64_t probe_tables = __builtin_amdgcn_s_memrealtime();
+    // a block from t_a to now, and its counts, into the wave's records
+    auto probe_block = [&](uint64_t t_a, uint32_t passes_tests) {
+        const uint64_t t_b = __builtin_amdgcn_s_memrealtime();
+        const uint32_t pw = blockIdx.x * (kBlock / kWave) + wave;
+        if (lane_id() == 0 && pw < (uint32_t)kProbeWaves && probe_blocks < (uint32_t)kProbeIters) {
+            uint64_t* r = carve_probe_blocks[pw * kProbeIters + probe_blocks];
+            r[0] = t_a;
+            r[1] = t_b;
+            r[2] = passes_tests;
+        }
+        ++probe_blocks;
+    };
+#endif
     // the tiles' loop, once with the job tables in LDS and once without (two
     // copies, so that neither reads its tables through generic pointers)
     auto tiles_loop = [&](auto in_lds) {
@@ -1851,15 +1863,7 @@ __global__ __launch_bounds__(kBlock, 7) void carve_frame_kernel(const fvv_job* _
                                  s_win[wave],
                           sils, tiles, tpr, tpc, g, i0 + xo, j0 + yo, k0, out + out_off, fb);
 #ifdef FVV_CARVE_PROBE
-        const uint64_t t_b = __builtin_amdgcn_s_memrealtime();
-        const uint32_t pw = blockIdx.x * (kBlock / kWave) + wave;
-        if (lane_id() == 0 && pw < (uint32_t)kProbeWaves && probe_blocks < (uint32_t)kProbeIters) {
-            uint64_t* r = carve_probe_blocks[pw * kProbeIters + probe_blocks];
-            r[0] = t_a;
-            r[1] = t_b;
-            r[2] = passes_tests;
-        }
-        ++probe_blocks;
+        probe_block(t_a, passes_tests);
 #else
         (void)passes_tests;
 #endif
@@ -1980,9 +1984,17 @@ __global__ __launch_bounds__(kBlock, 7) void carve_frame_kernel(const fvv_job* _
                 const int rank = __popc(mix & (uint32_t)lanes_below_mask());
                 const int sel = __builtin_amdgcn_ds_permute(
                     4 * (lane < 32 && ((mix >> (lane & 31)) & 1u) ? rank : 63), lane);
-                carve_block16<true>(cams, __popc(mix), sel, s_cam,
-                                    rho + (int64_t)jb * FVV_MAX_CAMS * kRhoPer, s_win[wave], sils,
-                                    tiles, tpr, tpc, g, i0, jy, kz, o, fb);
+#ifdef FVV_CARVE_PROBE
+                const uint64_t t_a = __builtin_amdgcn_s_memrealtime();
+#endif
+                const uint32_t passes_tests = carve_block16<true>(
+                    cams, __popc(mix), sel, s_cam, rho + (int64_t)jb * FVV_MAX_CAMS * kRhoPer,
+                    s_win[wave], sils, tiles, tpr, tpc, g, i0, jy, kz, o, fb);
+#ifdef FVV_CARVE_PROBE
+                probe_block(t_a, passes_tests);
+#else
+                (void)passes_tests;
+#endif
             }
             t = uniform(list.t) + lw.carve_blocks;
             par = uniform(list.par) ^ 1;

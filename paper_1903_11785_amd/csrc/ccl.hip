@@ -119,12 +119,17 @@ __device__ __forceinline__ void label_stamp_sync(int) {}
 #endif
 
 // ------------------------------------------------------------------ fine jobs of a frame
-// floor(a / b) for integers a, b held exactly in doubles, |a| < 2^53, b > 0:
-// the correctly rounded quotient never rounds up to the next integer n (a
-// non-integer a / b lies at least 1 / b below n, more than its rounding error
-// |a / b| 2^-53), so its floor is exact.
-__device__ __forceinline__ double floor_div_exact(double a, double b) {
-    return __builtin_floor(a / b);
+// floor(a / b) for integers a, b held exactly in doubles, |a| < 2^53, b > 0,
+// inv_b = 1 / b rounded, |a / b| < 2^24 (a frame's fine indices stay below 2^22):
+// the product's floor is within 1 of the quotient's, and the fma gives the
+// remainder exactly (an integer below 2^53), whose range says which way to
+// correct.  (A division per quotient made the labelling's last phases 0.7 us
+// longer.)
+__device__ __forceinline__ double floor_div_exact(double a, double b, double inv_b) {
+    double q = __builtin_floor(a * inv_b);
+    const double r = __builtin_fma(-q, b, a);
+    q += r < 0.0 ? -1.0 : r >= b ? 1.0 : 0.0;
+    return q;
 }
 
 constexpr int64_t kMaxKeyedSamples = 1431655765;  // 3*lin+axis must fit 32 bits
@@ -192,7 +197,7 @@ __device__ __forceinline__ void build_fine_jobs(const FrameJobs& fj, Box box, ui
     const uint32_t K = K_all < max_rois ? K_all : max_rois;
     // spacings and coarse indices are integers whose products stay below 2^52
     // (the frame's argument checks), exact in doubles
-    const double hc = (double)fj.hc_um, hf = (double)fj.hf_um;
+    const double hc = (double)fj.hc_um, hf = (double)fj.hf_um, inv_hf = 1.0 / hf;
     auto fine_lattice = [&](uint32_t t, fvv_grid& fg) -> int64_t {
         int32_t lo[3], hi[3];
         box(t, lo, hi);
@@ -202,10 +207,11 @@ __device__ __forceinline__ void build_fine_jobs(const FrameJobs& fj, Box box, ui
             const double c0 = (double)fj.coarse.lo[a];
             const double A = c0 + (double)(lo[a] - 1);
             const double B = c0 + (double)(hi[a] + 1);
-            double f0 = floor_div_exact(A * hc, hf);
-            double f1 = -floor_div_exact(-B * hc, hf);
-            const double fmin = -floor_div_exact(-c0 * hc, hf);
-            const double fmax = floor_div_exact((c0 + (double)(fj.coarse.dims[a] - 1)) * hc, hf);
+            double f0 = floor_div_exact(A * hc, hf, inv_hf);
+            double f1 = -floor_div_exact(-B * hc, hf, inv_hf);
+            const double fmin = -floor_div_exact(-c0 * hc, hf, inv_hf);
+            const double fmax =
+                floor_div_exact((c0 + (double)(fj.coarse.dims[a] - 1)) * hc, hf, inv_hf);
             f0 = f0 < fmin ? fmin : f0;
             f1 = f1 > fmax ? fmax : f1;
             fg.origin[a] = fj.coarse.origin[a];
@@ -302,6 +308,7 @@ __device__ __forceinline__ void build_fine_jobs(const FrameJobs& fj, Box box, ui
 // ------------------------------------------------------------------ run labelling
 constexpr int kMaskCap = 1024;   // row-mask words held in LDS (grids of up to 65536 rows)
 constexpr int kRowWords = 4;     // row-bitmap words a thread keeps in registers
+constexpr int kWaveRows = 128;   // row-mask words up to which a wave lists a word's rows
 
 // Rows, runs and forest: LDS arrays or their global-scratch twins.
 struct RunArrays {
@@ -400,24 +407,27 @@ __device__ __forceinline__ void stats_and_select(const LabelArgs& a, const RunAr
     for (int32_t j = threadIdx.x; j < K_all; j += NT) {
         int32_t* s = stats + (int64_t)kStatsRow * j;
         s[kStatCount] = 0;
-        s[kStatLo + 0] = s[kStatLo + 1] = s[kStatLo + 2] = 0x7fffffff;
+        s[kStatLo + 0] = s[kStatLo + 1] = 0x7fffffff;
         s[kStatHi + 0] = s[kStatHi + 1] = s[kStatHi + 2] = -1;
-        s[kStatMin] = 0x7fffffff;
     }
     __syncthreads();
     for (int32_t k = threadIdx.x; k < n_runs; k += NT) {
         const int32_t r = m.rrow[k];
-        const int32_t y = r % a.ny, z = r / a.ny;
+        const int2 yz = row_yz<kLds>(a, r);
+        const int32_t y = yz.x, z = yz.y;
         const int2 x = get_run<kLds>(m, k);
-        int32_t* s = stats + (int64_t)kStatsRow * rank_of<kLds>(m.P, k);
+        const int32_t p = ld<kLds>(m.P + k);
+        int32_t* s = stats + (int64_t)kStatsRow * (p < 0 ? -1 - p : -1 - ld<kLds>(m.P + p));
+        if (p < 0) {   // the root is the component's first run in raster order
+            s[kStatLo + 2] = z;
+            s[kStatMin] = (int32_t)((int64_t)a.nx * r + x.x);
+        }
         atomicAdd(&s[kStatCount], x.y - x.x + 1);
         atomicMin(&s[kStatLo + 0], x.x);
         atomicMax(&s[kStatHi + 0], x.y);
         atomicMin(&s[kStatLo + 1], y);
         atomicMax(&s[kStatHi + 1], y);
-        atomicMin(&s[kStatLo + 2], z);
         atomicMax(&s[kStatHi + 2], z);
-        atomicMin(&s[kStatMin], (int32_t)((int64_t)a.nx * r + x.x));
     }
     __syncthreads();
     uint32_t K = 0;
@@ -449,6 +459,41 @@ __device__ __forceinline__ void stats_and_select(const LabelArgs& a, const RunAr
         K += total;
     }
     *Kout = K;
+}
+
+// Row r as (y, z).  In LDS there are at most 65536 rows, where (r + 1/2) / ny
+// lies at least 1 / (2 ny) from an integer and the float product is within
+// 2^16 2^-22 / ny of it: the truncation is exact.
+template <bool kLds>
+__device__ __forceinline__ int2 row_yz(const LabelArgs& a, int32_t r) {
+    const int32_t z =
+        kLds ? (int32_t)(((float)r + 0.5f) * (1.0f / (float)a.ny)) : r / a.ny;
+    return make_int2(r - z * a.ny, z);
+}
+
+// Every run b adjacent to run k in its earlier neighbouring row q: (y-1, z) for
+// 0, (y-2+q, z-1) for 1 to 3.  A row's runs ascend in x, so the scan stops at
+// the first run starting past k's reach.
+template <bool kLds, typename F>
+__device__ __forceinline__ void for_each_adjacent_in_row(const LabelArgs& a, const RunArrays& m,
+                                                         int32_t k, int32_t q, F f) {
+    const int32_t r = m.rrow[k];
+    const int2 yz = row_yz<kLds>(a, r);
+    const int2 xk = get_run<kLds>(m, k);
+    const int32_t dy = q == 0 ? -1 : q - 2, dz = q == 0 ? 0 : -1;
+    const int32_t y = yz.x + dy;
+    if (y < 0 || y >= a.ny || yz.y + dz < 0)
+        return;
+    const int32_t j = row_index(m, r + dy + dz * a.ny);
+    if (j < 0)
+        return;
+    for (int32_t b = m.rs[j], be = m.rs[j + 1]; b < be; ++b) {
+        const int2 xb = get_run<kLds>(m, b);
+        if (xb.x > xk.y + 1)
+            break;
+        if (xb.y + 1 >= xk.x)
+            f(b);
+    }
 }
 
 // Every run b adjacent to run k in an earlier neighbouring row: (y-1, z) and
@@ -503,24 +548,35 @@ __device__ __forceinline__ bool label_body(const LabelArgs& a, const FrameJobs& 
     const int32_t wr = a.rb.wr;
     // 1. listed rows, ascending (the LDS row mask and its prefix are ready;
     //    the global twin builds the prefix here)
-    int32_t pos0 = 0;
-    for (int32_t base = 0; base < n_rm; base += NT) {
-        const int32_t w = base + threadIdx.x;
-        uint64_t bits;
-        int32_t pos;
-        if (kLds) {
-            bits = w < n_rm ? m.rm[w] : 0ull;
-            pos = w < n_rm ? m.rmpre[w] : 0;
-        } else {
-            bits = w < n_rm ? rowmask_word(a.rb, w, R) : 0ull;
-            uint32_t total;
-            pos = pos0 + (int32_t)block_exclusive_sum<NT>((uint32_t)__popcll(bits), scan, &total);
-            if (w < n_rm)
-                m.rmpre[w] = pos;
-            pos0 += (int32_t)total;
+    if (kLds && n_rm <= kWaveRows) {
+        // few mask words, with many rows each: a wave per word, lane = row
+        // (57 words: 0.5 us, a thread per word 1.4; 1013 words: 5.0)
+        for (int32_t w = threadIdx.x / kWave; w < n_rm; w += NT / kWave) {
+            const uint64_t bits = m.rm[w];
+            if ((bits >> lane_id()) & 1ull)
+                m.rows[m.rmpre[w] + (int32_t)lane_rank(bits)] = w * 64 + lane_id();
         }
-        for (uint64_t b = bits; b; b &= b - 1)
-            m.rows[pos++] = w * 64 + (__ffsll((unsigned long long)b) - 1);
+    } else {
+        int32_t pos0 = 0;
+        for (int32_t base = 0; base < n_rm; base += NT) {
+            const int32_t w = base + threadIdx.x;
+            uint64_t bits;
+            int32_t pos;
+            if (kLds) {
+                bits = w < n_rm ? m.rm[w] : 0ull;
+                pos = w < n_rm ? m.rmpre[w] : 0;
+            } else {
+                bits = w < n_rm ? rowmask_word(a.rb, w, R) : 0ull;
+                uint32_t total;
+                pos = pos0 +
+                      (int32_t)block_exclusive_sum<NT>((uint32_t)__popcll(bits), scan, &total);
+                if (w < n_rm)
+                    m.rmpre[w] = pos;
+                pos0 += (int32_t)total;
+            }
+            for (uint64_t b = bits; b; b &= b - 1)
+                m.rows[pos++] = w * 64 + (__ffsll((unsigned long long)b) - 1);
+        }
     }
     __syncthreads();
     label_stamp(2);
@@ -602,8 +658,14 @@ __device__ __forceinline__ bool label_body(const LabelArgs& a, const FrameJobs& 
         if (threadIdx.x == 0)
             *n_pairs = 0u;
         __syncthreads();
-        for (int32_t k = threadIdx.x; k < n_runs; k += NT)
-            for_each_earlier_adjacent<kLds>(a, m, k, [&](int32_t b) {
+        // a thread per (neighbouring row, run): with one per run the threads past
+        // the runs idled, and a thread's four rows waited for one another's
+        // appends (550 runs: 4.2 us, now 2.4).  Rows first: the unions of one
+        // run's neighbours side by side would contend (2.6 against 2.2 us)
+        for (int32_t kq = threadIdx.x; kq < 4 * n_runs; kq += NT) {
+            const int32_t q = (kq >= n_runs) + (kq >= 2 * n_runs) + (kq >= 3 * n_runs);
+            const int32_t k = kq - q * n_runs;
+            for_each_adjacent_in_row<kLds>(a, m, k, q, [&](int32_t b) {
                 const uint64_t act = __ballot(true);
                 const int leader = __ffsll((unsigned long long)act) - 1;
                 uint32_t base = 0;
@@ -616,6 +678,7 @@ __device__ __forceinline__ bool label_body(const LabelArgs& a, const FrameJobs& 
                 else
                     unite<kLds>(m.P, k, b);
             });
+        }
         __syncthreads();
         label_stamp(4);
         const uint32_t np = min(*n_pairs, (uint32_t)kPairCap);

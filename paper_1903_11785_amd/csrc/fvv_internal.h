@@ -92,16 +92,30 @@ __host__ __device__ inline float rounding_pad(const float* P, int W, int H, cons
     return (float)pad * (1.0f + 0x1p-20f);
 }
 
+// 1 / x to within a few ulps: on the GPU the hardware's estimate (2^-14 or
+// better) and three Newton steps, a fifth of a correctly rounded division's
+// instructions; the radii below allow 1e-9 for it.
+__host__ __device__ inline double recip64(double x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    double r = __builtin_amdgcn_rcp(x);
+    r = __builtin_fma(r, __builtin_fma(-x, r, 1.0), r);
+    r = __builtin_fma(r, __builtin_fma(-x, r, 1.0), r);
+    return __builtin_fma(r, __builtin_fma(-x, r, 1.0), r);
+#else
+    return 1.0 / x;
+#endif
+}
+
 // The corners' range of u and v and minimum of w (box_radius's first step,
 // shared by the radii of several half-extents over one box).
 struct BoxProj {
-    double umin, umax, vmin, vmax, wmin;
+    double umin, umax, vmin, vmax, wmin, inv_wmin;
 };
 
 __host__ __device__ inline BoxProj box_projection(const float* P, const double lo[3],
                                                   const double hi[3]) {
 #pragma clang fp contract(off)
-    BoxProj b{INFINITY, -INFINITY, INFINITY, -INFINITY, INFINITY};
+    BoxProj b{INFINITY, -INFINITY, INFINITY, -INFINITY, INFINITY, 0.0};
     for (int corner = 0; corner < 8; ++corner) {
         const double X[3] = {(corner & 1) ? hi[0] : lo[0], (corner & 2) ? hi[1] : lo[1],
                              (corner & 4) ? hi[2] : lo[2]};
@@ -115,13 +129,14 @@ __host__ __device__ inline BoxProj box_projection(const float* P, const double l
         if (r[2] > 0.0) {
             // (one reciprocal per corner: its rounding is far inside the
             // relative slack box_radius adds)
-            const double rw = 1.0 / r[2];
+            const double rw = recip64(r[2]);
             b.umin = fmin(b.umin, r[0] * rw);
             b.umax = fmax(b.umax, r[0] * rw);
             b.vmin = fmin(b.vmin, r[1] * rw);
             b.vmax = fmax(b.vmax, r[1] * rw);
         }
     }
+    b.inv_wmin = recip64(b.wmin);
     return b;
 }
 
@@ -148,8 +163,8 @@ __host__ __device__ inline void box_radius(const float* P, const BoxProj& b, con
         su += e[k] * fmax(fabs((double)P[k] - b.umin * wk), fabs((double)P[k] - b.umax * wk));
         sv += e[k] * fmax(fabs((double)P[4 + k] - b.vmin * wk), fabs((double)P[4 + k] - b.vmax * wk));
     }
-    *ru = su / b.wmin * (1.0 + 1e-9) + 1e-9;
-    *rv = sv / b.wmin * (1.0 + 1e-9) + 1e-9;
+    *ru = su * b.inv_wmin * (1.0 + 1e-9) + 1e-9;
+    *rv = sv * b.inv_wmin * (1.0 + 1e-9) + 1e-9;
 }
 
 // Radii of a frame's ROI lattices per (job, camera), kRhoPer floats each: the
