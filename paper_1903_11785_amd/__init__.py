@@ -103,7 +103,7 @@ JOB_DTYPE = np.dtype({"names": ["origin", "h", "lo", "dims", "cam_base", "n_cams
 CAMERA_DTYPE = np.dtype({"names": ["P", "width", "height"], "formats": [("<f4", 12), "<i4", "<i4"],
                          "offsets": [0, 48, 52], "itemsize": 56})
 assert C.sizeof(Job) == JOB_DTYPE.itemsize and C.sizeof(Roi) == ROI_DTYPE.itemsize
-assert C.sizeof(Camera) == CAMERA_DTYPE.itemsize
+assert C.sizeof(Camera) == CAMERA_DTYPE.itemsize and C.sizeof(SoftCamera) == 22 * 4
 
 
 # ------------------------------------------------------------------ library
@@ -207,14 +207,13 @@ class Grid:
 
 
 def make_cameras(P: np.ndarray, W: int, H: int):
+    # (one buffer copy: element by element, 16 cameras cost a call about 50 us)
     P = np.asarray(P, np.float32).reshape(-1, 12)
-    arr = (Camera * P.shape[0])()
-    for c in range(P.shape[0]):
-        for e in range(12):
-            arr[c].P[e] = float(P[c, e])
-        arr[c].width = int(W)
-        arr[c].height = int(H)
-    return arr
+    arr = np.empty(P.shape[0], CAMERA_DTYPE)
+    arr["P"] = P
+    arr["width"] = C.c_int32(int(W)).value
+    arr["height"] = C.c_int32(int(H)).value
+    return (Camera * P.shape[0]).from_buffer_copy(arr)
 
 
 def tile(tx: int = 64, tz: int = 4, persistent_blocks: int = 0) -> Tile:
@@ -599,14 +598,14 @@ def soft_cameras(K: np.ndarray, R0: np.ndarray, t0: np.ndarray, omega: np.ndarra
                  tau: np.ndarray):
     """SoftCamera ctypes array from K [N][4] (fx, fy, cx, cy), R0 [N][3][3],
     t0 [N][3], omega [N][3], tau [N][3] (host arrays)."""
-    K, R0, t0 = (np.asarray(a, np.float64) for a in (K, R0, t0))
-    omega, tau = (np.asarray(a, np.float64) for a in (omega, tau))
-    n = K.shape[0]
-    arr = (SoftCamera * n)()
-    for c in range(n):
-        arr[c].K[:] = [float(v) for v in K[c]]
-        arr[c].R0[:] = [float(v) for v in R0[c].reshape(-1)]
-        arr[c].t0[:] = [float(v) for v in t0[c]]
-        arr[c].omega[:] = [float(v) for v in omega[c]]
-        arr[c].tau[:] = [float(v) for v in tau[c]]
-    return arr
+    n = len(K)
+    arr = np.empty((n, 22), np.float32)
+    at = 0
+    with np.errstate(over="ignore"):        # (a double beyond float's range is an infinity)
+        for a, k in ((K, 4), (R0, 9), (t0, 3), (omega, 3), (tau, 3)):
+            a = np.asarray(a, np.float64)
+            if len(a) < n or (n and k != 9 and a.shape[1:2] != (k,)):
+                raise ValueError("soft_cameras: one row per camera of each argument")
+            arr[:, at:at + k] = a[:n].reshape(n, k)
+            at += k
+    return (SoftCamera * n).from_buffer_copy(arr)

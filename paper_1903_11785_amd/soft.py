@@ -45,6 +45,8 @@ def _pose_grads(gp, omega, tau):
     pose given as a plain array, which autograd does not track)."""
     like = lambda g, a: (g.to(device=a.device, dtype=a.dtype) if isinstance(a, torch.Tensor)
                          else None)
+    if all(isinstance(a, torch.Tensor) and a.device.type == "cpu" for a in (omega, tau)):
+        gp = gp.cpu()                 # one copy for both
     return like(gp[:, :3].contiguous(), omega), like(gp[:, 3:].contiguous(), tau)
 
 
