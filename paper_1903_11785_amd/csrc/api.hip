@@ -369,7 +369,7 @@ fvv_status fvv_create(fvv_ctx** out, const fvv_limits* lim) {
     A(d_sample_label, V)
     A(d_prefix, c->job_cap)
     A(d_job_pad, c->job_cap * FVV_MAX_CAMS)
-    A(d_soft_acc, FVV_MAX_CAMS * 6)
+    A(d_soft_acc, kSoftSlots * FVV_MAX_CAMS * 6)
     A(d_mesh_table, 1)
     A(d_job_single, 1)
     A(d_cams, FVV_MAX_CAMS)

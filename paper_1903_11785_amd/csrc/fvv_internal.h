@@ -601,7 +601,7 @@ struct fvv_ctx {
     // batched carve / frame
     fvv::JobPrefix* d_prefix;    // per job (max(max_jobs, max_rois) + 1)
     float* d_job_pad;            // rounding pad per (job, camera) of a batched carve
-    double* d_soft_acc;          // soft hull: per camera sum g and sum (R X) x g
+    double* d_soft_acc;          // soft hull: kSoftSlots times per camera sum g, sum (R X) x g
     fvv::MeshTable* d_mesh_table;  // marching-cubes configurations (built at creation)
     fvv_job* d_job_single;       // the job of a single-ROI fvv_surface call
     fvv_camera* d_cams;          // camera table of fvv_frame
@@ -749,6 +749,11 @@ struct SoftCam {
     float R[9];
     float t[3];
 };
+
+// Copies of the pose sums that a backward pass's workgroups add to in turn: up
+// to 8 workgroups per CU end at about the same time, and atomics on one address
+// go one after the other.
+constexpr int kSoftSlots = 16;
 
 struct SoftCamSet {
     SoftCam c[FVV_MAX_CAMS];
