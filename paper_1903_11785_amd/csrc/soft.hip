@@ -301,7 +301,8 @@ __device__ __forceinline__ int wave_min_i32(int v) {
 // What bounds it is latency and the sigmoids: bricks of 256 samples whose four
 // camera groups sampled all 16 cameras each (80 samplings per lattice sample for
 // the 16 needed here) with six barriers per camera took 67 us on 4.8e4 samples
-// of 16 cameras of 320 x 240, 37 now (16 of them the LDS atomics' own rate: copies of the
+// of 16 cameras of 320 x 240, 37 now (of 56 us at 8.6e4 samples 16 are the rate of the LDS
+// atomics themselves: copies of the
 // window against their conflicts gave nothing).
 constexpr int kBrick = 4;
 static_assert(kBrick * kBrick * kBrick == kWave, "a sample per lane");
