@@ -206,8 +206,12 @@ __global__ __launch_bounds__(kBlock) void pack_tiled_kernel(const uint8_t* __res
 // The same for images whose width is a multiple of 16 (masks 16-byte
 // aligned): one thread per two horizontally adjacent blocks, 16-byte loads of
 // its 8 rows, the two blocks' words in one 16-byte store and two bytes of
-// each packed row in one 2-byte store.
-template <bool k32, bool kAny>
+// each packed row in one 2-byte store.  kStream, for masks that no cache holds:
+// the 8 rows' loads are issued together, past the caches (they are read once,
+// and what the frame reads next stays).  10 and 24 masks of 3840 x 2160 (83 and
+// 199 MB): 22 and 51 us, 29 and 57 without; 16 of 1920 x 1080 (33 MB, the L2s'
+// size, held by them and the memory-side cache): 9.9 us, 7.8 without.
+template <bool k32, bool kAny, bool kStream>
 __global__ __launch_bounds__(kBlock) void pack_tiled16_kernel(const uint8_t* __restrict__ masks,
                                                               int n, int W, int H, int wpr,
                                                               int tpr, int tph, int bw,
@@ -236,10 +240,19 @@ __global__ __launch_bounds__(kBlock) void pack_tiled16_kernel(const uint8_t* __r
         const uint8_t* src = masks + ((int64_t)c * H + y0) * W + 8 * bx;
         uint8_t* dst = rows + ((int64_t)c * H + y0) * row_bytes + bx;
         uint64_t v0 = 0, v1 = 0;
+        typedef uint32_t Row16 __attribute__((ext_vector_type(4)));
+        Row16 rows16[8];
+        if (kStream) {
+#pragma unroll
+            for (int r = 0; r < 8; ++r)       // (rows past the image: its last again)
+                rows16[r] = __builtin_nontemporal_load(
+                    reinterpret_cast<const Row16*>(src + (int64_t)min(r, nr - 1) * W));
+        }
 #pragma unroll
         for (int r = 0; r < 8; ++r) {
             if (r < nr) {
-                const uint4 q = *reinterpret_cast<const uint4*>(src + (int64_t)r * W);
+                const Row16 q = kStream ? rows16[r]
+                                        : *reinterpret_cast<const Row16*>(src + (int64_t)r * W);
                 const uint32_t b0 = nonzero_bytes(q.x) | (nonzero_bytes(q.y) << 4);
                 const uint32_t b1 = nonzero_bytes(q.z) | (nonzero_bytes(q.w) << 4);
                 v0 |= (uint64_t)b0 << (8 * r);
@@ -258,6 +271,11 @@ __global__ __launch_bounds__(kBlock) void pack_tiled16_kernel(const uint8_t* __r
     }
 }
 
+// Bytes of masks from which they are streamed: 28 of 1920 x 1080 (58 MB) take
+// 14.5 us so and 13.5 without, 32 (66 MB) 17.0 and 17.9, 8 of 3840 x 2160 (66 MB)
+// 15.5 and 18.6.
+constexpr int64_t kStreamMasks = (int64_t)60 << 20;
+
 hipError_t launch_pack_tiled(int n, int W, int H, const uint8_t* masks, uint32_t* sils,
                              uint64_t* tiles, uint64_t* any, hipStream_t s) {
     if (W % 8 != 0 || reinterpret_cast<uintptr_t>(masks) % 8 != 0) {
@@ -271,9 +289,14 @@ hipError_t launch_pack_tiled(int n, int W, int H, const uint8_t* masks, uint32_t
         blocks = blocks < 1 ? 1 : (blocks > 65536 ? 65536 : blocks);
         const DivU32 dx = divu32_magic((uint32_t)(tpr / 2)), dy = divu32_magic((uint32_t)tph);
         const bool k32 = total + (int64_t)blocks * kBlock <= ((int64_t)1 << 32);
-        auto kernel = k32 ? (any ? pack_tiled16_kernel<true, true> : pack_tiled16_kernel<true, false>)
-                          : (any ? pack_tiled16_kernel<false, true>
-                                 : pack_tiled16_kernel<false, false>);
+        // (more blocks than 32 bits index are far more than any cache)
+        const bool stream = (int64_t)n * W * H >= kStreamMasks;
+        auto kernel = !k32 ? (any ? pack_tiled16_kernel<false, true, true>
+                                  : pack_tiled16_kernel<false, false, true>)
+                      : stream ? (any ? pack_tiled16_kernel<true, true, true>
+                                      : pack_tiled16_kernel<true, false, true>)
+                               : (any ? pack_tiled16_kernel<true, true, false>
+                                      : pack_tiled16_kernel<true, false, false>);
         hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kBlock), 0, s, masks, n, W, H,
                            wpr, tpr, tph, bw, dx, dy, sils, tiles, any);
         return hipGetLastError();
