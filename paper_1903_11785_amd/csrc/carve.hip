@@ -206,9 +206,9 @@ __global__ __launch_bounds__(kBlock) void pack_tiled_kernel(const uint8_t* __res
 // The same for images whose width is a multiple of 16 (masks 16-byte
 // aligned): one thread per two horizontally adjacent blocks, 16-byte loads of
 // its 8 rows, the two blocks' words in one 16-byte store and two bytes of
-// each packed row in one 2-byte store.  kStream, for masks that no cache holds:
-// the 8 rows' loads are issued together, past the caches (they are read once,
-// and what the frame reads next stays).  10 and 24 masks of 3840 x 2160 (83 and
+// each packed row in one 2-byte store.  kStream, for masks so large that they
+// come from memory: the 8 rows' loads are issued together, past the caches (they
+// are read once, and what the frame reads next stays).  10 and 24 masks of 3840 x 2160 (83 and
 // 199 MB): 22 and 51 us, 29 and 57 without; 16 of 1920 x 1080 (33 MB, the L2s'
 // size, held by them and the memory-side cache): 9.9 us, 7.8 without.
 template <bool k32, bool kAny, bool kStream>
