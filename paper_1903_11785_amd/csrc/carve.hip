@@ -2439,12 +2439,19 @@ __global__ __launch_bounds__(kBlock, 6) void carve_batched_culled_kernel(
     uint8_t* __restrict__ out) {
     __shared__ uint64_t s_off[kLds ? kBatchedJobLds + 1 : 1];
     __shared__ float s_cam[FVV_MAX_CAMS][13];
+    // the marks as the first wave read them, by turns (a turn's readers have
+    // passed the next one's barrier before it is written again).  All waves go by
+    // these: another workgroup may be writing the same bytes, where two jobs share
+    // output, and waves that each read them could disagree about the tiles and the
+    // barriers.  (852.9 us for 64 frames x 12 ROIs, 845.0 with each reading them;
+    // units read 64 at a time without barriers between spilled registers: 896.)
+    __shared__ uint64_t s_todo[2], s_live[2];
     const int nj = (int)counter[2];
     const auto off = load_offsets<kLds>(pre, nj, s_off);
     const XcdSlice xs = xcd_slice(off(nj));
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int lane = lane_id();
-    int staged = -1;
+    int staged = -1, todo_turn = 0, live_turn = 0;
     // the marks of 64 of the workgroup's units at a time, then the marked ones
     for (uint64_t base = xs.begin + xs.slot; base < xs.end; base += (uint64_t)xs.stride * kWave) {
         const uint64_t mine = base + (uint64_t)xs.stride * lane;
@@ -2453,10 +2460,14 @@ __global__ __launch_bounds__(kBlock, 6) void carve_batched_culled_kernel(
         if (mine < xs.end) {
             jl = upper_job(off, nj, mine);
             const BatchedUnit u = batched_unit(jobs[jl], (uint32_t)(mine - off(jl)));
-            kept = u.j0 < jobs[jl].grid.dims[1] && out[u.at] >= kDeadMark;
+            kept = wave == 0 && u.j0 < jobs[jl].grid.dims[1] && out[u.at] >= kDeadMark;
         }
-        uint64_t todo = __ballot(kept);
-        __syncthreads();   // every wave has read the marks, which the carve overwrites
+        const uint64_t marked = __ballot(kept);
+        if (threadIdx.x == 0)
+            s_todo[todo_turn] = marked;
+        __syncthreads();   // the marks are read; the carve overwrites them
+        uint64_t todo = uniform(s_todo[todo_turn]);
+        todo_turn ^= 1;
         for (; todo != 0ull; todo &= todo - 1ull) {
             const int bit = __ffsll((unsigned long long)todo) - 1;
             const int j = __builtin_amdgcn_readlane(jl, bit);
@@ -2479,12 +2490,18 @@ __global__ __launch_bounds__(kBlock, 6) void carve_batched_culled_kernel(
             }
             for (int x0 = 0; x0 < g.dims[0]; x0 += 16 * kWave) {
                 // 64 tiles' marks; a dead tile is zero but for its mark
-                const int x = x0 + 16 * lane;
-                const uint8_t mark = x < g.dims[0] ? p[x] : 0;
-                uint64_t live = __ballot(mark == kLiveMark);
-                __syncthreads();   // every wave has read the marks; the cameras are staged
-                if (wave == 0 && mark == kDeadMark)
-                    p[x] = 0;
+                if (wave == 0) {
+                    const int x = x0 + 16 * lane;
+                    const uint8_t mark = x < g.dims[0] ? p[x] : 0;
+                    const uint64_t marked = __ballot(mark == kLiveMark);
+                    if (lane == 0)
+                        s_live[live_turn] = marked;
+                    if (mark == kDeadMark)
+                        p[x] = 0;
+                }
+                __syncthreads();   // the marks are read; the cameras are staged
+                uint64_t live = uniform(s_live[live_turn]);
+                live_turn ^= 1;
                 // a tile per wave; one or two tiles are shared out in 4 or 2
                 // parts of 4 or 8 rows (the waves would idle)
                 const int nl = __popcll(live);
