@@ -481,24 +481,16 @@ __device__ __forceinline__ bool job_ok(const fvv_job& j) {
            j.out_offset >= 0;
 }
 
-// The units of a culled batched carve: kUnitY sample rows of 4 layers, all
-// along x, y fastest, the rows padded to groups of kUnitGroup units.
-constexpr int kUnitY = 16, kUnitGroup = 4;
-
-__device__ __forceinline__ uint64_t units_of_grid(const fvv_grid& g) {
-    constexpr int kRows = kUnitY * kUnitGroup;
-    return kUnitGroup * (uint64_t)((g.dims[1] + kRows - 1) / kRows) * (uint64_t)((g.dims[2] + 3) / 4);
-}
-
-// Prefix sums over a host-given job table by one workgroup: of tiles (TX x
-// TZ), or with kUnits of units; resets the work counter.  counter[0] = next
-// work item, [1] = tiles per item, [2] = jobs.  A job out of range gets no
-// tiles and raises the job flag.
-template <int TX, int TZ, bool kUnits>
-__device__ __forceinline__ void batched_prefix(const fvv_job* __restrict__ jobs, uint32_t n_jobs,
-                                               JobPrefix* __restrict__ pre,
-                                               uint32_t* __restrict__ counter,
-                                               uint32_t* __restrict__ status, uint32_t blocks) {
+// Prefix sums of the tiles over a host-given job table by one workgroup; resets
+// the work counter.  counter[0] = next work item, [1] = tiles per item, [2] =
+// jobs.  A job out of range gets no tiles and raises the job flag.
+template <int TX, int TZ>
+__global__ __launch_bounds__(kBlock) void batched_prepare_kernel(const fvv_job* __restrict__ jobs,
+                                                                 uint32_t n_jobs,
+                                                                 JobPrefix* __restrict__ pre,
+                                                                 uint32_t* __restrict__ counter,
+                                                                 uint32_t* __restrict__ status,
+                                                                 uint32_t blocks) {
     __shared__ uint64_t scratch[kBlock / kWave];
     __shared__ uint64_t carry;
     if (threadIdx.x == 0)
@@ -509,7 +501,7 @@ __device__ __forceinline__ void batched_prefix(const fvv_job* __restrict__ jobs,
         uint64_t t = 0;
         if (j < n_jobs) {
             if (job_ok(jobs[j]))
-                t = kUnits ? units_of_grid(jobs[j].grid) : tiles_of_grid(jobs[j].grid, TX, TZ);
+                t = tiles_of_grid(jobs[j].grid, TX, TZ);
             else
                 atomicOr(status, kFlagJob);
         }
@@ -530,16 +522,6 @@ __device__ __forceinline__ void batched_prefix(const fvv_job* __restrict__ jobs,
         counter[1] = grab_size(total, blocks);
         counter[2] = n_jobs;
     }
-}
-
-template <int TX, int TZ>
-__global__ __launch_bounds__(kBlock) void batched_prepare_kernel(const fvv_job* __restrict__ jobs,
-                                                                 uint32_t n_jobs,
-                                                                 JobPrefix* __restrict__ pre,
-                                                                 uint32_t* __restrict__ counter,
-                                                                 uint32_t* __restrict__ status,
-                                                                 uint32_t blocks) {
-    batched_prefix<TX, TZ, false>(jobs, n_jobs, pre, counter, status, blocks);
 }
 
 template <int TX, int TZ, bool kFineBits>
@@ -2048,8 +2030,8 @@ __global__ __launch_bounds__(kBlock, 7) void carve_frame_kernel(const fvv_job* _
 // Most of a batch is empty (98.6 % on 64 frames x 12 ROIs of two ellipsoids),
 // so what it cannot do without is writing zeros.  Three passes:
 //   1. batched_zero_kernel zeroes every job's output, each workgroup a
-//      contiguous part of a job, as fast as a plain fill; its first workgroups
-//      write the unit prefix and the rounding pads.
+//      contiguous part of a job; its first workgroups write the unit prefix and
+//      the rounding pads.
 //   2. batched_mark_kernel classifies the cameras for units (kUnitY sample
 //      rows x 4 layers, all along x), a wave per kUnitGroup of them, the group
 //      as a whole first, and then for the tiles (16 samples along x) of a unit
@@ -2068,6 +2050,15 @@ constexpr int kBatchedJobLds = 1024;
 constexpr int kGroup = kBlock / kWave;
 constexpr int kRowRectWords = 8;   // silhouette words per row of a unit's rectangle
 constexpr uint8_t kLiveMark = 0xff, kDeadMark = 0xfe;   // no occupancy values
+
+// The units of a culled batched carve: kUnitY sample rows of 4 layers, all
+// along x, y fastest, the rows padded to groups of kUnitGroup units.
+constexpr int kUnitY = 16, kUnitGroup = 4;
+
+__device__ __forceinline__ uint64_t units_of_grid(const fvv_grid& g) {
+    constexpr int kRows = kUnitY * kUnitGroup;
+    return kUnitGroup * (uint64_t)((g.dims[1] + kRows - 1) / kRows) * (uint64_t)((g.dims[2] + 3) / 4);
+}
 
 // The first n_off(m) prefixes of the jobs in LDS (kLds) or from the table.
 template <bool kLds>
@@ -2121,53 +2112,160 @@ struct LdsCams {
     __device__ float padc(int c) const { return cam[c][12]; }
 };
 
-// Workgroup 0: the unit prefix.  The next pad_blocks: the rounding pad of every
-// (job, camera) pair over the job's lattice box, job_pad[j * FVV_MAX_CAMS + c].
-// The rest, `parts` per job: zeros, each part from one multiple of 4 KB of the
-// address to another (lines are written whole but at a job's ends), 16 bytes a
-// lane.  2.9e9 bytes take 522 us, 5.6 TB/s; in address order over all jobs
-// they take 487, but that needs the prefix first: a launch more, which a small
-// batch (a few us in all) pays as much as a large one.
+// The zeroing pass's steps: a job's output in pieces of kZeroStep bytes, cut at
+// the address's multiples of it (lines are written whole but at a job's ends).
+constexpr uint64_t kZeroStep = kBlock * 16;
+
+struct JobBytes {
+    uintptr_t p0, p1;
+    __device__ uint64_t steps() const { return (p1 - 1) / kZeroStep - p0 / kZeroStep + 1; }
+};
+
+__device__ __forceinline__ JobBytes job_bytes(const fvv_job& j, const uint8_t* out) {
+    const uintptr_t p0 = (uintptr_t)(out + j.out_offset);
+    return JobBytes{p0, p0 + (uintptr_t)((uint64_t)j.grid.dims[0] * (uint64_t)j.grid.dims[1] *
+                                         (uint64_t)j.grid.dims[2])};
+}
+
+// A table's prefixes go kPrefixJobs jobs per thread (their loads in flight
+// together): a workgroup takes 1024 jobs at once.
+constexpr int kPrefixJobs = 4;
+static_assert(kBlock * kPrefixJobs == kBatchedJobLds, "an LDS table in one step");
+
+// Workgroup 0: the unit prefix; a job out of range has no units and raises the
+// job flag.  The next: the rounding pad of every (job, camera) pair over the
+// job's lattice box, job_pad[j * FVV_MAX_CAMS + c].
+__device__ __forceinline__ void batched_table(uint32_t block, const fvv_job* __restrict__ jobs,
+                                              uint32_t n_jobs, const fvv_camera* __restrict__ cams,
+                                              float* __restrict__ job_pad,
+                                              JobPrefix* __restrict__ pre,
+                                              uint32_t* __restrict__ counter,
+                                              uint32_t* __restrict__ status) {
+    if (block == 0) {
+        __shared__ uint64_t scratch[kBlock / kWave];
+        uint64_t units = 0;
+        for (uint32_t base = 0; base < n_jobs; base += kBatchedJobLds) {
+            const uint32_t j0 = base + kPrefixJobs * threadIdx.x;
+            uint64_t u[kPrefixJobs], us = 0;
+#pragma unroll
+            for (int e = 0; e < kPrefixJobs; ++e) {
+                u[e] = 0;
+                if (j0 + e < n_jobs) {
+                    if (job_ok(jobs[j0 + e]))
+                        u[e] = units_of_grid(jobs[j0 + e].grid);
+                    else
+                        atomicOr(status, kFlagJob);
+                }
+                us += u[e];
+            }
+            uint64_t total;
+            uint64_t at = units + block_exclusive_sum64<kBlock>(us, scratch, &total);
+#pragma unroll
+            for (int e = 0; e < kPrefixJobs; ++e)
+                if (j0 + e < n_jobs) {
+                    pre[j0 + e].tile_off = at;
+                    at += u[e];
+                }
+            units += total;
+        }
+        if (threadIdx.x == 0) {
+            pre[n_jobs].tile_off = units;
+            counter[2] = n_jobs;
+        }
+        return;
+    }
+    const uint64_t p = (uint64_t)(block - 1) * kBlock + threadIdx.x;
+    if (p >= (uint64_t)n_jobs * FVV_MAX_CAMS)
+        return;
+    const fvv_job& j = jobs[p / FVV_MAX_CAMS];
+    const int c = (int)(p % FVV_MAX_CAMS);
+    if (!job_ok(j) || c >= j.n_cams)
+        return;
+    double lo[3], hi[3];
+    grid_box(j.grid, lo, hi);
+    job_pad[p] = rounding_pad(cams[j.cam_base + c].P, j.width, j.height, lo, hi);
+}
+
+// Zero steps [q, end) of a job's output by the workgroup.
+__device__ __forceinline__ void zero_steps(const JobBytes& b, uint64_t q, uint64_t end) {
+    uintptr_t at = (b.p0 & ~(uintptr_t)(kZeroStep - 1)) + q * kZeroStep + 16 * threadIdx.x;
+    for (; q < end; ++q, at += kZeroStep) {
+        if (at >= b.p0 && at + 16 <= b.p1) {
+            *reinterpret_cast<uint4*>(at) = make_uint4(0u, 0u, 0u, 0u);
+        } else {
+            for (int k = 0; k < 16; ++k)
+                if (at + k >= b.p0 && at + k < b.p1)
+                    *reinterpret_cast<uint8_t*>(at + k) = 0;
+        }
+    }
+}
+
+// Zeros all jobs' outputs.  Workgroups [0, table): batched_table's work.  The
+// next `shared`: what jobs are longer than parts * kPartSteps steps, in equal
+// shares over 1024 jobs at a time, whatever the jobs' sizes.  The rest, `parts`
+// per job: the job's first parts * kPartSteps steps.  (Without the shared ones a
+// batch took as long as its largest job's few workgroups: 3147 us for 767 small
+// ROIs and one of 1e9 samples, 481 now; parts of 256 and 512 steps: 486, 502.  All
+// steps in equal shares over the table need a sum over the table in every
+// workgroup: 5 to 20 us more for 768 jobs.)
+constexpr uint64_t kPartSteps = 128;
+
 __global__ __launch_bounds__(kBlock) void batched_zero_kernel(
     const fvv_job* __restrict__ jobs, uint32_t n_jobs, const fvv_camera* __restrict__ cams,
     float* __restrict__ job_pad, JobPrefix* __restrict__ pre, uint32_t* __restrict__ counter,
-    uint32_t* __restrict__ status, uint32_t pad_blocks, uint32_t parts, uint8_t* __restrict__ out) {
-    if (blockIdx.x == 0) {
-        batched_prefix<64, 4, true>(jobs, n_jobs, pre, counter, status, 1u);
+    uint32_t* __restrict__ status, uint32_t table, uint32_t shared, uint32_t parts,
+    uint8_t* __restrict__ out) {
+    if (blockIdx.x < table) {
+        batched_table(blockIdx.x, jobs, n_jobs, cams, job_pad, pre, counter, status);
         return;
     }
-    if (blockIdx.x <= pad_blocks) {
-        const uint64_t p = (uint64_t)(blockIdx.x - 1) * kBlock + threadIdx.x;
-        if (p >= (uint64_t)n_jobs * FVV_MAX_CAMS)
+    const uint64_t most = (uint64_t)parts * kPartSteps;
+    if (blockIdx.x >= table + shared) {
+        const uint32_t z = blockIdx.x - table - shared, jn = z / parts, part = z - jn * parts;
+        if (!job_ok(jobs[jn]))
             return;
-        const fvv_job& j = jobs[p / FVV_MAX_CAMS];
-        const int c = (int)(p % FVV_MAX_CAMS);
-        if (!job_ok(j) || c >= j.n_cams)
-            return;
-        double lo[3], hi[3];
-        grid_box(j.grid, lo, hi);
-        job_pad[p] = rounding_pad(cams[j.cam_base + c].P, j.width, j.height, lo, hi);
+        const JobBytes b = job_bytes(jobs[jn], out);
+        const uint64_t all = b.steps(), steps = all < most ? all : most;
+        zero_steps(b, steps * part / parts, steps * (part + 1) / parts);
         return;
     }
-    const uint32_t z = blockIdx.x - 1 - pad_blocks, jn = z / parts, part = z - jn * parts;
-    const fvv_job& j = jobs[jn];
-    if (!job_ok(j))
-        return;
-    constexpr uint64_t kStep = kBlock * 16;
-    const uintptr_t p0 = (uintptr_t)(out + j.out_offset);
-    const uintptr_t p1 = p0 + (uintptr_t)((uint64_t)j.grid.dims[0] * (uint64_t)j.grid.dims[1] *
-                                          (uint64_t)j.grid.dims[2]);
-    const uintptr_t a0 = p0 & ~(uintptr_t)(kStep - 1);
-    const uint64_t steps = (p1 - a0 + kStep - 1) / kStep;
-    for (uint64_t q = steps * part / parts; q < steps * (part + 1) / parts; ++q) {
-        const uintptr_t at = a0 + q * kStep + 16 * threadIdx.x;
-        if (at >= p0 && at + 16 <= p1) {
-            *reinterpret_cast<uint4*>(at) = make_uint4(0u, 0u, 0u, 0u);
-        } else {
-            for (int b = 0; b < 16; ++b)
-                if (at + b >= p0 && at + b < p1)
-                    *reinterpret_cast<uint8_t*>(at + b) = 0;
+    __shared__ uint64_t s_step[kBatchedJobLds + 1];
+    __shared__ uint64_t scratch[kBlock / kWave];
+    for (uint32_t base = 0; base < n_jobs; base += kBatchedJobLds) {
+        const uint32_t j0 = kPrefixJobs * threadIdx.x;
+        uint64_t z[kPrefixJobs], zs = 0, total;
+#pragma unroll
+        for (int e = 0; e < kPrefixJobs; ++e) {
+            z[e] = 0;
+            if (base + j0 + e < n_jobs && job_ok(jobs[base + j0 + e])) {
+                const uint64_t all = job_bytes(jobs[base + j0 + e], out).steps();
+                z[e] = all > most ? all - most : 0ull;
+            }
+            zs += z[e];
         }
+        uint64_t at = block_exclusive_sum64<kBlock>(zs, scratch, &total);
+        if (total == 0)
+            continue;
+#pragma unroll
+        for (int e = 0; e < kPrefixJobs; ++e) {
+            s_step[j0 + e] = at;
+            at += z[e];
+        }
+        if (threadIdx.x == 0)
+            s_step[kBatchedJobLds] = total;
+        __syncthreads();
+        uint64_t q = total * (blockIdx.x - table) / shared;
+        const uint64_t q1 = total * (blockIdx.x - table + 1) / shared;
+        auto off = [&](int m) { return s_step[m]; };
+        int jn = upper_job(off, kBatchedJobLds, q);
+        while (q < q1) {
+            while (off(jn + 1) <= q)      // (most jobs have nothing left)
+                ++jn;
+            const uint64_t first = off(jn), end = off(jn + 1) < q1 ? off(jn + 1) : q1;
+            zero_steps(job_bytes(jobs[base + jn], out), most + (q - first), most + (end - first));
+            q = end;
+        }
+        __syncthreads();
     }
 }
 
@@ -2654,12 +2752,16 @@ hipError_t launch_carve_batched(fvv_ctx* ctx, const fvv_job* jobs, uint32_t n_jo
         const uint64_t pairs = (uint64_t)n_jobs * FVV_MAX_CAMS;
         // the first two passes' waves stay resident: eight workgroups per CU
         const unsigned rblocks = (unsigned)((ctx->n_cus * 8 + kXcds - 1) / kXcds * kXcds);
-        const unsigned pad_blocks = (unsigned)((pairs + kBlock - 1) / kBlock);
-        // at least about 16 zeroing workgroups per CU
-        const unsigned parts = ((unsigned)ctx->n_cus * 16 + n_jobs - 1) / n_jobs;
-        hipLaunchKernelGGL(batched_zero_kernel, dim3(1 + pad_blocks + n_jobs * parts),
+        const unsigned table = 1u + (unsigned)((pairs + kBlock - 1) / kBlock);
+        // zeroing: a workgroup per CU for the long jobs' rest (four times fewer for a
+        // large table, whose sum takes each of them a while: one writes 57 GB/s), and
+        // at least about 16 per CU for the jobs' parts
+        const unsigned cus = (unsigned)ctx->n_cus;
+        const unsigned shared = n_jobs <= (uint32_t)kBatchedJobLds ? cus : (cus + 3) / 4;
+        const unsigned parts = (cus * 16 + n_jobs - 1) / n_jobs;
+        hipLaunchKernelGGL(batched_zero_kernel, dim3(table + shared + n_jobs * parts),
                            dim3(kBlock), 0, s, jobs, n_jobs, cams, ctx->d_job_pad, ctx->d_prefix,
-                           ctx->d_counter, ctx->d_status, pad_blocks, parts, out);
+                           ctx->d_counter, ctx->d_status, table, shared, parts, out);
         if (n_jobs <= (uint32_t)kBatchedJobLds) {
             hipLaunchKernelGGL((batched_mark_kernel<true>), dim3(rblocks), dim3(kBlock), 0, s,
                                jobs, ctx->d_prefix, ctx->d_counter, cams, ctx->d_job_pad, sils,
