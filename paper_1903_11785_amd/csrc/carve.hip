@@ -2209,6 +2209,7 @@ __device__ __forceinline__ void zero_steps(const JobBytes& b, uint64_t q, uint64
 // steps in equal shares over the table need a sum over the table in every
 // workgroup: 5 to 20 us more for 768 jobs.)
 constexpr uint64_t kPartSteps = 128;
+constexpr uint64_t kMostZero = 1 << 20;   // workgroups of one launch (they loop beyond)
 
 __global__ __launch_bounds__(kBlock) void batched_zero_kernel(
     const fvv_job* __restrict__ jobs, uint32_t n_jobs, const fvv_camera* __restrict__ cams,
@@ -2221,12 +2222,15 @@ __global__ __launch_bounds__(kBlock) void batched_zero_kernel(
     }
     const uint64_t most = (uint64_t)parts * kPartSteps;
     if (blockIdx.x >= table + shared) {
-        const uint32_t z = blockIdx.x - table - shared, jn = z / parts, part = z - jn * parts;
-        if (!job_ok(jobs[jn]))
-            return;
-        const JobBytes b = job_bytes(jobs[jn], out);
-        const uint64_t all = b.steps(), steps = all < most ? all : most;
-        zero_steps(b, steps * part / parts, steps * (part + 1) / parts);
+        const uint64_t n = (uint64_t)n_jobs * parts;
+        for (uint64_t z = blockIdx.x - table - shared; z < n; z += gridDim.x - table - shared) {
+            const uint32_t jn = (uint32_t)(z / parts), part = (uint32_t)(z - (uint64_t)jn * parts);
+            if (!job_ok(jobs[jn]))
+                continue;
+            const JobBytes b = job_bytes(jobs[jn], out);
+            const uint64_t all = b.steps(), steps = all < most ? all : most;
+            zero_steps(b, steps * part / parts, steps * (part + 1) / parts);
+        }
         return;
     }
     __shared__ uint64_t s_step[kBatchedJobLds + 1];
@@ -2759,7 +2763,9 @@ hipError_t launch_carve_batched(fvv_ctx* ctx, const fvv_job* jobs, uint32_t n_jo
         const unsigned cus = (unsigned)ctx->n_cus;
         const unsigned shared = n_jobs <= (uint32_t)kBatchedJobLds ? cus : (cus + 3) / 4;
         const unsigned parts = (cus * 16 + n_jobs - 1) / n_jobs;
-        hipLaunchKernelGGL(batched_zero_kernel, dim3(table + shared + n_jobs * parts),
+        const uint64_t zeroing = (uint64_t)n_jobs * parts;
+        hipLaunchKernelGGL(batched_zero_kernel,
+                           dim3(table + shared + (unsigned)(zeroing < kMostZero ? zeroing : kMostZero)),
                            dim3(kBlock), 0, s, jobs, n_jobs, cams, ctx->d_job_pad, ctx->d_prefix,
                            ctx->d_counter, ctx->d_status, table, shared, parts, out);
         if (n_jobs <= (uint32_t)kBatchedJobLds) {
