@@ -2056,8 +2056,9 @@ constexpr uint8_t kLiveMark = 0xff, kDeadMark = 0xfe;   // no occupancy values
 constexpr int kUnitY = 16, kUnitGroup = 4;
 
 __device__ __forceinline__ uint64_t units_of_grid(const fvv_grid& g) {
-    constexpr int kRows = kUnitY * kUnitGroup;
-    return kUnitGroup * (uint64_t)((g.dims[1] + kRows - 1) / kRows) * (uint64_t)((g.dims[2] + 3) / 4);
+    constexpr uint32_t kRows = kUnitY * kUnitGroup;   // (unsigned: a side may be near 2^31)
+    return kUnitGroup * (uint64_t)(((uint32_t)g.dims[1] + kRows - 1u) / kRows) *
+           (uint64_t)((g.dims[2] + 3) / 4);
 }
 
 // The first n_off(m) prefixes of the jobs in LDS (kLds) or from the table.
@@ -2079,18 +2080,21 @@ __device__ __forceinline__ JobOffsets<kLds> load_offsets(const JobPrefix* __rest
     return JobOffsets<kLds>{lds, pre};
 }
 
-// Unit u of a job: its first row (past the lattice for a padding unit) and
-// layer, and the place of its first byte.
+// Unit u of a job: whether it has rows in the lattice (padding units do not), its
+// first row and layer, and the place of its first byte.
 struct BatchedUnit {
+    bool on;
     int j0, k0;
     int64_t at;
 };
 
 __device__ __forceinline__ BatchedUnit batched_unit(const fvv_job& job, uint32_t u) {
-    constexpr int kRows = kUnitY * kUnitGroup;
-    const uint32_t nuy = kUnitGroup * (uint32_t)((job.grid.dims[1] + kRows - 1) / kRows);
+    constexpr uint32_t kRows = kUnitY * kUnitGroup;
+    const uint32_t nuy = kUnitGroup * (((uint32_t)job.grid.dims[1] + kRows - 1u) / kRows);
     BatchedUnit b;
-    b.j0 = (int)(u % nuy) * kUnitY;
+    const uint32_t j0 = u % nuy * kUnitY;
+    b.on = j0 < (uint32_t)job.grid.dims[1];
+    b.j0 = b.on ? (int)j0 : 0;
     b.k0 = (int)(u / nuy) * 4;
     b.at = job.out_offset +
            ((int64_t)b.k0 * job.grid.dims[1] + b.j0) * (int64_t)job.grid.dims[0];
@@ -2363,27 +2367,31 @@ __global__ __launch_bounds__(kBlock, 8) void batched_mark_kernel(
         const BatchedUnit u = batched_unit(job, (uint32_t)(unit - off(j)));
         auto rejected = [&](int j0, int rows) {
             float lo[3], hi[3];
-            box_corners(g, 0, g.dims[0] - 1, j0, min(j0 + rows, g.dims[1]) - 1, u.k0,
+            box_corners(g, 0, g.dims[0] - 1, j0, j0 + min(rows, g.dims[1] - j0) - 1, u.k0,
                         min(u.k0 + 4, g.dims[2]) - 1, lo, hi);
             uint32_t rej, mix;
             classify_box_wave<kRowRectWords, true>(jc, sils + job.sil_base,
                                                    (int64_t)jc.H * jc.wpr, lo, hi, rej, mix);
             return rej != 0u;
         };
-        if (u.j0 >= g.dims[1] || (per > 1 && rejected(u.j0, kUnitY * kUnitGroup)))
+        if (!u.on || (per > 1 && rejected(u.j0, kUnitY * kUnitGroup)))
             continue;
         for (int q = 0; q < per; ++q) {
+            if (q * kUnitY >= g.dims[1] - u.j0)
+                break;
             const int j0 = u.j0 + q * kUnitY;
-            if (j0 >= g.dims[1] || rejected(j0, kUnitY))
+            if (rejected(j0, kUnitY))
                 continue;
             // its tiles, 16 at a time: lane (b, c) = (tile, camera of four)
             const int lane = lane_id(), b = lane & 15, cl = lane >> 4;
-            for (int i0 = 16 * b; __ballot(i0 < g.dims[0]) != 0ull; i0 += 256) {
+            const uint32_t nx = (uint32_t)g.dims[0];   // (unsigned: the steps go past nx)
+            for (uint32_t x = 16 * b; __ballot(x < nx) != 0ull; x += 256) {
                 float lo[3], hi[3];
-                box_corners(g, min(i0, g.dims[0] - 1), min(i0 + 16, g.dims[0]) - 1, j0,
-                            min(j0 + kUnitY, g.dims[1]) - 1, u.k0, min(u.k0 + 4, g.dims[2]) - 1,
+                const int i0 = (int)min(x, nx - 1u);
+                box_corners(g, i0, i0 + min(16, g.dims[0] - i0) - 1, j0,
+                            j0 + min(kUnitY, g.dims[1] - j0) - 1, u.k0, min(u.k0 + 4, g.dims[2]) - 1,
                             lo, hi);
-                uint32_t live = (uint32_t)(__ballot(i0 < g.dims[0]) & 0xffffull);
+                uint32_t live = (uint32_t)(__ballot(x < nx) & 0xffffull);
                 for (int cb = 0; cb < jc.n && live != 0u; cb += 4) {
                     const int c = cb + cl;
                     int cls = kCullMixed;
@@ -2394,7 +2402,7 @@ __global__ __launch_bounds__(kBlock, 8) void batched_mark_kernel(
                                              lo, hi, win, org);
                     live &= ~any_camera16(__ballot(cls == kCullReject));
                 }
-                if (lane < 16 && i0 < g.dims[0])
+                if (lane < 16 && x < nx)
                     out[u.at + (int64_t)q * kUnitY * g.dims[0] + i0] =
                         (live >> b) & 1u ? kLiveMark : kDeadMark;
             }
@@ -2425,7 +2433,8 @@ __device__ __forceinline__ uint64_t carve_tile16(const Cams& cams,
     const int si = i0 + 4 * (b & 3), sj = j0 + 4 * (b >> 2);
     const bool sb_on = si < nx && sj < ny && ((sub >> b) & 1u);
     float lo[3], hi[3];
-    box_corners(g, min(si, nx - 1), min(si + 4, nx) - 1, min(sj, ny - 1), min(sj + 4, ny) - 1, k0,
+    const int bi = min(si, nx - 1), bj = min(sj, ny - 1);
+    box_corners(g, bi, bi + min(4, nx - bi) - 1, bj, bj + min(4, ny - bj) - 1, k0,
                 min(k0 + 4, nz) - 1, lo, hi);
     // sample masks of the sub-block's x, y and z inside the lattice
     uint64_t occ = 0ull;
@@ -2562,7 +2571,7 @@ __global__ __launch_bounds__(kBlock, 6) void carve_batched_culled_kernel(
         if (mine < xs.end) {
             jl = upper_job(off, nj, mine);
             const BatchedUnit u = batched_unit(jobs[jl], (uint32_t)(mine - off(jl)));
-            kept = wave == 0 && u.j0 < jobs[jl].grid.dims[1] && out[u.at] >= kDeadMark;
+            kept = wave == 0 && u.on && out[u.at] >= kDeadMark;
         }
         const uint64_t marked = __ballot(kept);
         if (threadIdx.x == 0)
@@ -2590,11 +2599,12 @@ __global__ __launch_bounds__(kBlock, 6) void carve_batched_culled_kernel(
                 }
                 staged = j;
             }
-            for (int x0 = 0; x0 < g.dims[0]; x0 += 16 * kWave) {
+            const uint32_t nx = (uint32_t)g.dims[0];   // (unsigned: the steps go past nx)
+            for (uint32_t x0 = 0; x0 < nx; x0 += 16 * kWave) {
                 // 64 tiles' marks; a dead tile is zero but for its mark
                 if (wave == 0) {
-                    const int x = x0 + 16 * lane;
-                    const uint8_t mark = x < g.dims[0] ? p[x] : 0;
+                    const uint32_t x = x0 + 16 * lane;
+                    const uint8_t mark = x < nx ? p[x] : 0;
                     const uint64_t marked = __ballot(mark == kLiveMark);
                     if (lane == 0)
                         s_live[live_turn] = marked;
@@ -2613,11 +2623,11 @@ __global__ __launch_bounds__(kBlock, 6) void carve_batched_culled_kernel(
                 for (int q = 0; live != 0ull; live &= live - 1ull, ++q) {
                     if (q % (kGroup / parts) != wave / parts)
                         continue;
-                    const int i0 = x0 + 16 * (__ffsll((unsigned long long)live) - 1);
+                    const int i0 = (int)x0 + 16 * (__ffsll((unsigned long long)live) - 1);
                     const uint32_t row =
                         tile16_row(carve_tile16(jc, sils + job.sil_base, g, i0, u.j0, u.k0, sub));
                     const int y = lane & 15, z = lane >> 4;
-                    if (u.j0 + y < g.dims[1] && u.k0 + z < g.dims[2] && y / rows == part)
+                    if (y < g.dims[1] - u.j0 && u.k0 + z < g.dims[2] && y / rows == part)
                         store_row16(p + ((int64_t)z * g.dims[1] + y) * g.dims[0] + i0, row,
                                     min(16, g.dims[0] - i0));
                 }
