@@ -1037,7 +1037,7 @@ __global__ __launch_bounds__(kBlock) void carve_kept_kernel(const CamSet cams,
 
 // Camera classification of a whole culled tile (TX x TY x 4 samples from
 // i0, j0, k0) by one wave: rejecting and mixed cameras, uniform over the wave.
-template <int TX, class Cams>
+template <int TX, int kWords = 2, class Cams>
 __device__ __forceinline__ void classify_tile(const Cams& cams, const uint32_t* __restrict__ sils,
                                               const fvv_grid& g, int i0, int j0, int k0,
                                               uint32_t& reject, uint32_t& mixed) {
@@ -1045,7 +1045,7 @@ __device__ __forceinline__ void classify_tile(const Cams& cams, const uint32_t* 
     float lo[3], hi[3];
     box_corners(g, i0, min(i0 + TX, g.dims[0]) - 1, j0, min(j0 + TY, g.dims[1]) - 1, k0,
                 min(k0 + 4, g.dims[2]) - 1, lo, hi);
-    classify_box_wave<2>(cams, sils, (int64_t)cams.H * cams.wpr, lo, hi, reject, mixed);
+    classify_box_wave<kWords>(cams, sils, (int64_t)cams.H * cams.wpr, lo, hi, reject, mixed);
 }
 
 // One culled tile (first sample i0, j0, k0).  tile_off (uniform): a camera
@@ -2027,25 +2027,25 @@ __global__ __launch_bounds__(kBlock, 7) void carve_frame_kernel(const fvv_job* _
 }
 
 // ------------------------------------------------------------------ batched carve, culled
-// Most of a batch is empty (98.6 % on 64 frames x 12 ROIs of two ellipsoids),
-// so what it cannot do without is writing zeros.  Three passes:
+// Most of a large batch is empty (98.6 % on 64 frames x 12 ROIs of two
+// ellipsoids), so what it cannot do without is writing zeros.  Three passes:
 //   1. batched_zero_kernel zeroes every job's output, each workgroup a
-//      contiguous part of a job; its first workgroups write the unit prefix and
+//      contiguous part of a job; its first workgroups write the prefixes and
 //      the rounding pads.
 //   2. batched_mark_kernel classifies the cameras for units (kUnitY sample
 //      rows x 4 layers, all along x), a wave per kUnitGroup of them, the group
 //      as a whole first, and then for the tiles (16 samples along x) of a unit
 //      that no camera rejects, 16 at a time.  Such a unit's tiles get a mark
 //      in their first byte: kLiveMark, or kDeadMark where a camera rejects the
-//      tile.
+//      tile.  A small batch it carves itself (carve_strips).
 //   3. carve_batched_culled_kernel carves the live tiles of the marked units,
 //      a wave each.
 // The units and tiles go to the XCDs in a static partition; each job's cameras
-// come from the device table.  64 frames x 12 ROIs (2.9e9 samples, 4 cameras)
-// take 522 + 104 + 200 us; one pass that classified and wrote a row of tiles
-// per workgroup and step took 1258 us, 2.3 TB/s.  A first pass that zeroed the
-// rejected units itself took 636 us whatever it classified: its 2.5 KB spans
-// at odd addresses reach 4.2 TB/s.
+// come from the device table.  64 frames x 12 ROIs (2.7e9 samples, 4 cameras)
+// take 518 + 101 + 215 us (a plain fill of as many bytes 398); one pass that
+// classified and wrote a row of tiles per workgroup and step took 1258 us.  A
+// first pass that zeroed the rejected units itself took 636 us whatever it
+// classified: its 2.5 KB spans at odd addresses reach 4.2 TB/s.
 constexpr int kBatchedJobLds = 1024;
 constexpr int kGroup = kBlock / kWave;
 constexpr int kRowRectWords = 8;   // silhouette words per row of a unit's rectangle
@@ -2061,23 +2061,42 @@ __device__ __forceinline__ uint64_t units_of_grid(const fvv_grid& g) {
            (uint64_t)((g.dims[2] + 3) / 4);
 }
 
-// The first n_off(m) prefixes of the jobs in LDS (kLds) or from the table.
-template <bool kLds>
+// The jobs' prefixes of units, or with kStrips of strips, in LDS (kLds) or from
+// the table.
+template <bool kLds, bool kStrips>
 struct JobOffsets {
     const uint64_t* lds;
     const JobPrefix* pre;
-    __device__ uint64_t operator()(int m) const { return kLds ? lds[m] : pre[m].tile_off; }
+    __device__ uint64_t operator()(int m) const {
+        return kLds ? lds[m] : kStrips ? pre[m].bit_off : pre[m].tile_off;
+    }
 };
 
-template <bool kLds>
-__device__ __forceinline__ JobOffsets<kLds> load_offsets(const JobPrefix* __restrict__ pre,
-                                                         int nj, uint64_t* lds) {
+template <bool kLds, bool kStrips = false>
+__device__ __forceinline__ JobOffsets<kLds, kStrips> load_offsets(
+    const JobPrefix* __restrict__ pre, int nj, uint64_t* lds) {
     if (kLds) {
         for (int j = threadIdx.x; j <= nj; j += kBlock)
-            lds[j] = pre[j].tile_off;
+            lds[j] = kStrips ? pre[j].bit_off : pre[j].tile_off;
         __syncthreads();
     }
-    return JobOffsets<kLds>{lds, pre};
+    return JobOffsets<kLds, kStrips>{lds, pre};
+}
+
+// A small batch (kStripTiles tiles of 64 x 4 x 4 samples, 24 per CU) is carved by
+// strips instead, kStripY sample rows of 4 layers, all along x, y fastest, in the
+// marking's place (the third pass finds no units): with so few units the marks
+// cost a launch's latency and leave most of the chip idle.  32 tight ROIs of 2e6
+// samples in all (3385 tiles) in 4, 16 and 32 cameras: 32, 50 and 113 us, by
+// marks 38, 91 and 191; 6 ROIs of 6.6e5: 21.4 and 26.6; 12 of 1.1e6 in 16 cameras,
+// nearly empty: 24 and 34.  Above, 36 nearly empty ROIs of 3.8e6 (6233 tiles) in 4
+// cameras: 32.5 and 30.6, 32 tight ones of 5.6e6 (8079): 47 and 42.
+constexpr int kStripY = 4;
+constexpr uint64_t kStripTiles = 6144;
+
+__device__ __forceinline__ uint64_t strips_of_grid(const fvv_grid& g) {
+    return (uint64_t)(((uint32_t)g.dims[1] + kStripY - 1u) / kStripY) *
+           (uint64_t)((g.dims[2] + 3) / 4);
 }
 
 // Unit u of a job: whether it has rows in the lattice (padding units do not), its
@@ -2136,8 +2155,9 @@ __device__ __forceinline__ JobBytes job_bytes(const fvv_job& j, const uint8_t* o
 constexpr int kPrefixJobs = 4;
 static_assert(kBlock * kPrefixJobs == kBatchedJobLds, "an LDS table in one step");
 
-// Workgroup 0: the unit prefix; a job out of range has no units and raises the
-// job flag.  The next: the rounding pad of every (job, camera) pair over the
+// Workgroup 0: the prefixes of units (tile_off; no units in all where the batch
+// goes by strips) and of strips (bit_off); a job out of range has none and raises
+// the job flag.  The next: the rounding pad of every (job, camera) pair over the
 // job's lattice box, job_pad[j * FVV_MAX_CAMS + c].
 __device__ __forceinline__ void batched_table(uint32_t block, const fvv_job* __restrict__ jobs,
                                               uint32_t n_jobs, const fvv_camera* __restrict__ cams,
@@ -2147,33 +2167,45 @@ __device__ __forceinline__ void batched_table(uint32_t block, const fvv_job* __r
                                               uint32_t* __restrict__ status) {
     if (block == 0) {
         __shared__ uint64_t scratch[kBlock / kWave];
-        uint64_t units = 0;
+        uint64_t units = 0, strips = 0, tiles = 0;
         for (uint32_t base = 0; base < n_jobs; base += kBatchedJobLds) {
             const uint32_t j0 = base + kPrefixJobs * threadIdx.x;
-            uint64_t u[kPrefixJobs], us = 0;
+            uint64_t u[kPrefixJobs], r[kPrefixJobs], us = 0, rs = 0;
 #pragma unroll
             for (int e = 0; e < kPrefixJobs; ++e) {
-                u[e] = 0;
+                u[e] = r[e] = 0;
                 if (j0 + e < n_jobs) {
-                    if (job_ok(jobs[j0 + e]))
-                        u[e] = units_of_grid(jobs[j0 + e].grid);
-                    else
+                    const fvv_job& j = jobs[j0 + e];
+                    if (job_ok(j)) {
+                        u[e] = units_of_grid(j.grid);
+                        r[e] = strips_of_grid(j.grid);
+                        tiles += r[e] * (((uint32_t)j.grid.dims[0] + 63u) / 64u);
+                    } else {
                         atomicOr(status, kFlagJob);
+                    }
                 }
                 us += u[e];
+                rs += r[e];
             }
-            uint64_t total;
-            uint64_t at = units + block_exclusive_sum64<kBlock>(us, scratch, &total);
+            uint64_t ut, rt;
+            uint64_t ua = units + block_exclusive_sum64<kBlock>(us, scratch, &ut);
+            uint64_t ra = strips + block_exclusive_sum64<kBlock>(rs, scratch, &rt);
 #pragma unroll
             for (int e = 0; e < kPrefixJobs; ++e)
                 if (j0 + e < n_jobs) {
-                    pre[j0 + e].tile_off = at;
-                    at += u[e];
+                    pre[j0 + e].tile_off = ua;
+                    pre[j0 + e].bit_off = ra;
+                    ua += u[e];
+                    ra += r[e];
                 }
-            units += total;
+            units += ut;
+            strips += rt;
         }
+        uint64_t all;
+        block_exclusive_sum64<kBlock>(tiles, scratch, &all);
         if (threadIdx.x == 0) {
-            pre[n_jobs].tile_off = units;
+            pre[n_jobs].tile_off = all <= kStripTiles ? 0ull : units;
+            pre[n_jobs].bit_off = strips;
             counter[2] = n_jobs;
         }
         return;
@@ -2215,7 +2247,7 @@ __device__ __forceinline__ void zero_steps(const JobBytes& b, uint64_t q, uint64
 constexpr uint64_t kPartSteps = 128;
 constexpr uint64_t kMostZero = 1 << 20;   // workgroups of one launch (they loop beyond)
 
-__global__ __launch_bounds__(kBlock) void batched_zero_kernel(
+__global__ __launch_bounds__(kBlock, 8) void batched_zero_kernel(
     const fvv_job* __restrict__ jobs, uint32_t n_jobs, const fvv_camera* __restrict__ cams,
     float* __restrict__ job_pad, JobPrefix* __restrict__ pre, uint32_t* __restrict__ counter,
     uint32_t* __restrict__ status, uint32_t table, uint32_t shared, uint32_t parts,
@@ -2335,6 +2367,50 @@ __device__ __forceinline__ uint32_t any_camera16(uint64_t m) {
     return (uint32_t)((m | (m >> 16) | (m >> 32) | (m >> 48)) & 0xffffull);
 }
 
+// A small batch in one pass, a workgroup per strip: the cameras classified for
+// four tiles of 64 samples along x at once, a wave each, then those that no
+// camera rejects carved by the workgroup (the output is zero before).
+template <bool kLds>
+__device__ __forceinline__ void carve_strips(const fvv_job* __restrict__ jobs, int nj,
+                                             const JobPrefix* __restrict__ pre,
+                                             const fvv_camera* __restrict__ cams,
+                                             const float* __restrict__ job_pad,
+                                             const uint32_t* __restrict__ sils,
+                                             uint8_t* __restrict__ out, uint64_t* lds) {
+    constexpr uint32_t TX = kBlock / kStripY;
+    __shared__ int32_t s_cls[kGroup][2];      // rejecting, mixed cameras
+    const auto off = load_offsets<kLds, true>(pre, nj, lds);
+    const XcdSlice xs = xcd_slice(off(nj));
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    for (uint64_t strip = xs.begin + xs.slot; strip < xs.end; strip += xs.stride) {
+        const int j = __builtin_amdgcn_readfirstlane(upper_job(off, nj, strip));
+        const fvv_job& job = jobs[j];
+        const fvv_grid g = job.grid;
+        const JobCams jc = job_cams(job, j, cams, job_pad);
+        const uint32_t r = (uint32_t)(strip - off(j));
+        const uint32_t nty = ((uint32_t)g.dims[1] + kStripY - 1u) / kStripY;
+        const int j0 = (int)(r % nty) * kStripY, k0 = (int)(r / nty) * 4;
+        for (uint32_t x0 = 0; x0 < (uint32_t)g.dims[0]; x0 += TX * kGroup) {
+            __syncthreads();                  // the last tiles are done with s_cls
+            if (x0 + TX * wave < (uint32_t)g.dims[0]) {
+                uint32_t rej, mix;
+                classify_tile<TX, kRowRectWords>(jc, sils + job.sil_base, g, (int)(x0 + TX * wave),
+                                                 j0, k0, rej, mix);
+                if (lane_id() == 0) {
+                    s_cls[wave][0] = (int32_t)rej;
+                    s_cls[wave][1] = (int32_t)mix;
+                }
+            }
+            __syncthreads();
+            for (int w = 0; w < kGroup && x0 + TX * w < (uint32_t)g.dims[0]; ++w)
+                if (uniform(s_cls[w][0]) == 0)
+                    carve_tile_culled<TX>(jc, sils + job.sil_base, g, (int)(x0 + TX * w), j0, k0,
+                                          out + job.out_offset, RowBits{}, false,
+                                          (uint32_t)uniform(s_cls[w][1]));
+        }
+    }
+}
+
 template <bool kLds>
 __global__ __launch_bounds__(kBlock, 8) void batched_mark_kernel(
     const fvv_job* __restrict__ jobs, const JobPrefix* __restrict__ pre,
@@ -2343,6 +2419,10 @@ __global__ __launch_bounds__(kBlock, 8) void batched_mark_kernel(
     uint8_t* __restrict__ out) {
     __shared__ uint64_t s_off[kLds ? kBatchedJobLds + 1 : 1];
     const int nj = (int)counter[2];
+    if (pre[nj].tile_off == 0) {
+        carve_strips<kLds>(jobs, nj, pre, cams, job_pad, sils, out, s_off);
+        return;
+    }
     const auto off = load_offsets<kLds>(pre, nj, s_off);
     // units one by one while there is a wave for each (a wave then waits for
     // two classifications), else group by group (most groups are rejected with
@@ -2769,10 +2849,11 @@ hipError_t launch_carve_batched(fvv_ctx* ctx, const fvv_job* jobs, uint32_t n_jo
         const unsigned table = 1u + (unsigned)((pairs + kBlock - 1) / kBlock);
         // zeroing: a workgroup per CU for the long jobs' rest (four times fewer for a
         // large table, whose sum takes each of them a while: one writes 57 GB/s), and
-        // at least about 16 per CU for the jobs' parts
+        // for the jobs' parts 64 per job, at least 1 and at most about 16 per CU
         const unsigned cus = (unsigned)ctx->n_cus;
         const unsigned shared = n_jobs <= (uint32_t)kBatchedJobLds ? cus : (cus + 3) / 4;
-        const unsigned parts = (cus * 16 + n_jobs - 1) / n_jobs;
+        const unsigned most_zero = cus * 16, few = n_jobs < most_zero / 64 ? n_jobs * 64 : most_zero;
+        const unsigned parts = ((few < cus ? cus : few) + n_jobs - 1) / n_jobs;
         const uint64_t zeroing = (uint64_t)n_jobs * parts;
         hipLaunchKernelGGL(batched_zero_kernel,
                            dim3(table + shared + (unsigned)(zeroing < kMostZero ? zeroing : kMostZero)),

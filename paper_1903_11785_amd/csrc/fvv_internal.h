@@ -474,7 +474,7 @@ constexpr int kStatsRow = 8;   // per component: count, lo[3], hi[3], smallest l
 // crossing-edge work item (exclusive prefix sums over the job table).
 struct JobPrefix {
     uint64_t tile_off;   // first tile of the job (culled batched carve: first unit)
-    uint64_t bit_off;    // first word of the job's fine bitmap
+    uint64_t bit_off;    // first word of the job's fine bitmap (culled batched carve: first strip)
     uint32_t item_off;   // first crossing-edge work item of the job
     uint32_t pad;
 };
