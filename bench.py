@@ -115,8 +115,7 @@ def sources_sha256(paths):
 BATCHED_KERNEL = {"kernel": "carve_batched_culled_kernel",
                   "sources": ["paper_1903_11785_amd/csrc/carve.hip",
                               "paper_1903_11785_amd/csrc/fvv_internal.h"],
-                  "traffic": "profiles/carve_batched_culled_kernel_batched_traffic.json",
-                  "tile": [16, 16, 4]}
+                  "traffic": "profiles/carve_batched_culled_kernel_batched_traffic.json"}
 
 
 VIS_KERNELS = {"kernel": "depth_clear_kernel + depth_raster_kernel + visibility_kernel",
@@ -503,12 +502,12 @@ def batched_leg(args, fvv, torch):
         "per_roi_graph_ms_p50": p_ms, "per_roi_eager_wall_ms": eager_ms,
         "speedup_vs_per_roi": p_ms / b_ms, "identical_to_per_roi": identical,
         # compulsory bytes only: one occupancy byte per sample written; traffic from
-        # the stored counter runs (taken with the 16x16x4 tile)
+        # the stored counter runs (of a depth-4 tile)
         "roofline": {"kernel": "carve_batched_culled_kernel", "bound": "hbm",
                      "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "bytes_per_launch": int(total),
                      "traffic": (stored_traffic(BATCHED_KERNEL)
-                                 if [t.tx, t.ty, t.tz] == BATCHED_KERNEL["tile"] else None)},
+                                 if t.tz == 4 else None)},
     }
 
 

@@ -1,7 +1,9 @@
 """Tile autotuner of the batched fine carve (Sec. II-B-3 over many ROIs).
 
 The bytes ``fvv_carve_batched`` writes do not depend on the tile; only its
-speed does.  The best tile depends on:
+speed does.  Tiles of depth 4 cull cameras and launch the same work whatever
+their width and workgroups, so one of them is timed; other depths test every
+sample against every camera.  The best tile depends on:
 - the camera count and image size;
 - how many pixels one fine sample spans, which sets how often a 4x4x4 box of
   samples is decided by its corner rectangle alone;
@@ -24,19 +26,18 @@ import numpy as np
 
 from . import JOB_DTYPE, Tile, tile
 
-# (tx, tz) shapes and persistent-grid multiples of the CU count tried by default:
-# depth 4 is the culled kernel (static XCD split), the others test every
-# camera with dynamic tile grabbing.
-CULLED_SHAPES = ((64, 4), (32, 4), (16, 4))
+# (tx, tz) shapes tried by default, and the multiples of the CU count that their
+# persistent grids take: depth 4 culls (its kernels choose their own grids), the
+# others test every camera with dynamic tile grabbing.
+CULLED_SHAPES = ((64, 4),)
 PLAIN_SHAPES = ((64, 1), (64, 2), (32, 2), (64, 8))
-GRID_MULTIPLES = (8, 32, 64, 128)
+GRID_MULTIPLES = (8,)
 
 
 def candidates(n_cus: int) -> List[Tile]:
     """Default candidate tiles for a device with n_cus compute units."""
-    out = [tile(tx, tz, n_cus * m) for (tx, tz) in CULLED_SHAPES for m in GRID_MULTIPLES]
-    out += [tile(tx, tz, n_cus * 8) for (tx, tz) in PLAIN_SHAPES]
-    return out
+    return [tile(tx, tz, n_cus * m) for (tx, tz) in CULLED_SHAPES + PLAIN_SHAPES
+            for m in GRID_MULTIPLES]
 
 
 def pixels_per_sample(P_table: np.ndarray, jobs: np.ndarray) -> float:
