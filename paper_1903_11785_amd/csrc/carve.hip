@@ -1737,7 +1737,9 @@ __device__ uint64_t carve_probe_waves[kProbeWaves][3];
 // alone), 380 by groups; whole frames of 8, 13, 24, 28 and 30e6 samples (16 to
 // 24 cameras) 176, 285, 298, 330 and 297 us against 176, 298, 330, 353 and 367.
 // Smaller ones lose by it (5e6 samples of 56 ROIs: 267 against 255, a frame of
-// 4e6: the carve 49 against 42).
+// 4e6: the carve 49 against 42).  A large frame of more than kJobLds ROIs goes by
+// tiles: 8.4e7 samples of 82 ROIs in 16 cameras take the carve 403 us, where 5.9e7
+// of 57 take 200 (1.4 times as long per sample).
 constexpr int kJobLds = 64;
 constexpr int kGroupBricks = 64;
 constexpr uint64_t kGroupTiles = 12288, kWideGroupTiles = 65536;
@@ -2041,8 +2043,8 @@ __global__ __launch_bounds__(kBlock, 7) void carve_frame_kernel(const fvv_job* _
 //   3. carve_batched_culled_kernel carves the live tiles of the marked units,
 //      a wave each.
 // The units and tiles go to the XCDs in a static partition; each job's cameras
-// come from the device table.  64 frames x 12 ROIs (2.7e9 samples, 4 cameras)
-// take 518 + 101 + 215 us (a plain fill of as many bytes 398); one pass that
+// come from the device table.  64 frames x 12 ROIs (2.9e9 samples, 4 cameras)
+// take 530 + 103 + 201 us (a plain fill of as many bytes 415); one pass that
 // classified and wrote a row of tiles per workgroup and step took 1258 us.  A
 // first pass that zeroed the rejected units itself took 636 us whatever it
 // classified: its 2.5 KB spans at odd addresses reach 4.2 TB/s.
