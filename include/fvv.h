@@ -215,8 +215,9 @@ fvv_status fvv_surface_noalloc(const fvv_grid *roi, const uint8_t *d_occ_fine, i
                                uint32_t *d_n_points, hipStream_t stream);
 
 /* Batched fine carving (Sec. II-B-3 over many ROIs, of one or many frames) in
- * ONE persistent launch.  d_jobs: n_jobs jobs (device, <= max_jobs); d_cams:
- * device camera table; output bytes as each job states.  The output is
+ * two or three launches, whatever their number.  d_jobs: n_jobs jobs (device, <=
+ * max_jobs); d_cams: device camera table; output bytes as each job states (jobs
+ * may share output bytes where they write the same).  The output is
  * byte-identical to carving each job with fvv_carve, whatever the tile.
  * With tile->tz == 4 (and for tile == NULL, the default 64x4x4 tile) the
  * cameras are culled per 4x4x4 box of samples (a camera whose padded pixel
