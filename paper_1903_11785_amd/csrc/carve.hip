@@ -1037,7 +1037,7 @@ __global__ __launch_bounds__(kBlock) void carve_kept_kernel(const CamSet cams,
 
 // Camera classification of a whole culled tile (TX x TY x 4 samples from
 // i0, j0, k0) by one wave: rejecting and mixed cameras, uniform over the wave.
-template <int TX, int kWords = 2, class Cams>
+template <int TX, int kWords = 2, bool kStop = false, class Cams>
 __device__ __forceinline__ void classify_tile(const Cams& cams, const uint32_t* __restrict__ sils,
                                               const fvv_grid& g, int i0, int j0, int k0,
                                               uint32_t& reject, uint32_t& mixed) {
@@ -1045,7 +1045,7 @@ __device__ __forceinline__ void classify_tile(const Cams& cams, const uint32_t* 
     float lo[3], hi[3];
     box_corners(g, i0, min(i0 + TX, g.dims[0]) - 1, j0, min(j0 + TY, g.dims[1]) - 1, k0,
                 min(k0 + 4, g.dims[2]) - 1, lo, hi);
-    classify_box_wave<kWords>(cams, sils, (int64_t)cams.H * cams.wpr, lo, hi, reject, mixed);
+    classify_box_wave<kWords, kStop>(cams, sils, (int64_t)cams.H * cams.wpr, lo, hi, reject, mixed);
 }
 
 // One culled tile (first sample i0, j0, k0).  tile_off (uniform): a camera
@@ -2085,16 +2085,19 @@ __device__ __forceinline__ JobOffsets<kLds, kStrips> load_offsets(
     return JobOffsets<kLds, kStrips>{lds, pre};
 }
 
-// A small batch (kStripTiles tiles of 64 x 4 x 4 samples, 24 per CU) is carved by
-// strips instead, kStripY sample rows of 4 layers, all along x, y fastest, in the
-// marking's place (the third pass finds no units): with so few units the marks
-// cost a launch's latency and leave most of the chip idle.  32 tight ROIs of 2e6
-// samples in all (3385 tiles) in 4, 16 and 32 cameras: 32, 50 and 113 us, by
-// marks 38, 91 and 191; 6 ROIs of 6.6e5: 21.4 and 26.6; 12 of 1.1e6 in 16 cameras,
-// nearly empty: 24 and 34.  Above, 36 nearly empty ROIs of 3.8e6 (6233 tiles) in 4
-// cameras: 32.5 and 30.6, 32 tight ones of 5.6e6 (8079): 47 and 42.
+// A small batch (kStripTiles tiles of 64 x 4 x 4 samples, 48 per CU; those of a few
+// cameras count twice) is carved by strips instead, kStripY sample rows of 4
+// layers, all along x, y fastest, in the marking's place (the third pass finds no
+// units): with so few units the marks cost a launch's latency and leave most of
+// the chip idle, the more so the more cameras a unit waits for.  32 tight ROIs of
+// 2e6 samples in all (3385 tiles) in 4, 16 and 32 cameras: 32, 50 and 113 us, by
+// marks 38, 91 and 191; 6 ROIs of 6.6e5: 21.4 and 26.6; nearly empty ones of 6e6
+// (10190 tiles) in 12 and 32 cameras: 60 and 81, by marks 85 and 126.  Above, 32
+// tight ROIs of 5.6e6 in 4 cameras (8079 tiles, counted twice): 47 and 42 by
+// marks; 128 of 1e7 in 16 cameras (15397): 86 and 68.
 constexpr int kStripY = 4;
-constexpr uint64_t kStripTiles = 6144;
+constexpr uint64_t kStripTiles = 12288;
+constexpr int kFewCams = 6;
 
 __device__ __forceinline__ uint64_t strips_of_grid(const fvv_grid& g) {
     return (uint64_t)(((uint32_t)g.dims[1] + kStripY - 1u) / kStripY) *
@@ -2181,7 +2184,8 @@ __device__ __forceinline__ void batched_table(uint32_t block, const fvv_job* __r
                     if (job_ok(j)) {
                         u[e] = units_of_grid(j.grid);
                         r[e] = strips_of_grid(j.grid);
-                        tiles += r[e] * (((uint32_t)j.grid.dims[0] + 63u) / 64u);
+                        tiles += r[e] * (((uint32_t)j.grid.dims[0] + 63u) / 64u) *
+                                 (j.n_cams <= kFewCams ? 2u : 1u);
                     } else {
                         atomicOr(status, kFlagJob);
                     }
@@ -2396,7 +2400,7 @@ __device__ __forceinline__ void carve_strips(const fvv_job* __restrict__ jobs, i
             __syncthreads();                  // the last tiles are done with s_cls
             if (x0 + TX * wave < (uint32_t)g.dims[0]) {
                 uint32_t rej, mix;
-                classify_tile<TX, kRowRectWords>(jc, sils + job.sil_base, g, (int)(x0 + TX * wave),
+                classify_tile<TX, kRowRectWords, true>(jc, sils + job.sil_base, g, (int)(x0 + TX * wave),
                                                  j0, k0, rej, mix);
                 if (lane_id() == 0) {
                     s_cls[wave][0] = (int32_t)rej;

@@ -1,6 +1,6 @@
 """Both routes of a culled batched carve (Sec. II-B-3) at their edges, byte for byte
 against the oracle, with the bytes between the jobs untouched: strips of 4 rows up
-to 6144 tiles of 64 x 4 x 4 samples, marks above; marks unit by unit up to 128 units
+to 12288 tiles of 64 x 4 x 4 samples (a job of up to 6 cameras counts twice), marks above; marks unit by unit up to 128 units
 per CU, above in groups of 4 whose cameras are left at the first four that reject;
 tables inside the LDS and past it.  The jobs' cameras (4, 9 and 17) and images
 differ from job to job, so a workgroup that takes several units takes new cameras
@@ -23,8 +23,8 @@ def _units(d):
     return 4 * -(-d[1] // 64) * -(-d[2] // 4)
 
 
-def _tiles(d):
-    return -(-d[0] // 64) * -(-d[1] // 4) * -(-d[2] // 4)
+def _tiles(f, d):
+    return -(-d[0] // 64) * -(-d[1] // 4) * -(-d[2] // 4) * (2 if f == 0 else 1)
 
 
 def _frames():
@@ -38,8 +38,8 @@ def _frames():
 
 @pytest.mark.parametrize("copies,marks,groups,lds", [
     (1, False, False, True),
-    (4, False, False, True),
-    (5, True, False, True),
+    (7, False, False, True),
+    (8, True, False, True),
     (68, True, False, True),
     (69, True, True, True),
     (85, True, True, True),
@@ -52,7 +52,7 @@ def test_routes_at_their_edges(copies, marks, groups, lds, h_um):
     import paper_1903_11785_amd as fvv
     n_cus = torch.cuda.get_device_properties(0).multi_processor_count
     table = BOXES * copies
-    assert (sum(_tiles(d) for _, d in table) > 6144) == marks
+    assert (sum(_tiles(f, d) for f, d in table) > 12288) == marks
     assert (sum(_units(d) for _, d in table) > 128 * n_cus) == groups
     assert (len(table) <= 1024) == lds
     frames, h, gap = _frames(), scenes.um_to_h(h_um), 5
