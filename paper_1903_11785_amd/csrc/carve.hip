@@ -2094,7 +2094,7 @@ __device__ __forceinline__ JobOffsets<kLds, kStrips> load_offsets(
 // marks 38, 91 and 191; 6 ROIs of 6.6e5: 21.4 and 26.6; nearly empty ones of 6e6
 // (10190 tiles) in 12 and 32 cameras: 60 and 81, by marks 85 and 126.  Above, 32
 // tight ROIs of 5.6e6 in 4 cameras (8079 tiles, counted twice): 47 and 42 by
-// marks; 128 of 1e7 in 16 cameras (15397): 86 and 68.
+// marks; 128 nearly empty ones of 1e7 in 8 cameras (15397): 64 and 59.
 constexpr int kStripY = 4;
 constexpr uint64_t kStripTiles = 12288;
 constexpr int kFewCams = 6;
